@@ -100,6 +100,60 @@ bool invert_cols(V3 a, V3 b, V3 c, double inv[9], double& det) {
     return true;
 }
 
+// The triangles around every lateral node, over all diamonds and in cyclic order
+// (six, or five at the twelve icosahedron vertices), starting with the first one in
+// (diamond, i, j, wedge) order: every copy of a node has the same list, so a kernel that
+// gathers over it writes the same bits to every copy and needs no interface sum.
+// ring_tri[slot][r] = 8 (cell column) + 4 (wedge) + (the node's lateral index in it), -1
+// past the last; triangle r has the node's neighbours nb[r] and nb[r + 1] (cyclically) as
+// its lateral vertices lat + 1 and lat + 2; ring_nb holds their slots (in the triangle's
+// own diamond; entry 5 of a five-ring repeats entry 0).
+void build_rings(Level& L) {
+    const int m = L.m, m1 = m + 1;
+    const int di[2][3] = {{0, 1, 0}, {1, 0, 1}}, dj[2][3] = {{0, 0, 1}, {1, 1, 0}};
+    auto slot = [&](int d, int i, int j) { return (d * m1 + i) * m1 + j; };
+    std::vector<int> cnt(L.n_unique_lat, 0), tri((size_t)L.n_unique_lat * 6, -1);
+    for (int d = 0; d < 10; ++d)
+        for (int i = 0; i < m; ++i)
+            for (int j = 0; j < m; ++j)
+                for (int w = 0; w < 2; ++w)
+                    for (int l = 0; l < 3; ++l) {
+                        const int u = L.uid[slot(d, i + di[w][l], j + dj[w][l])];
+                        if (cnt[u] == 6) throw Error(TNG_E_INVAL, "mesh build: more than six triangles at a node");
+                        tri[(size_t)u * 6 + cnt[u]++] = 8 * ((d * m + i) * m + j) + 4 * w + l;
+                    }
+    // slot of the lateral vertex (lat + s) mod 3 of a coded triangle
+    auto vertex = [&](int code, int s) {
+        const int c = code >> 3, w = (code >> 2) & 1, l = ((code & 3) + s) % 3;
+        return slot(c / (m * m), (c / m) % m + di[w][l], c % m + dj[w][l]);
+    };
+    std::vector<int> nb((size_t)L.n_unique_lat * 6);
+    for (int u = 0; u < L.n_unique_lat; ++u) {
+        int* t = &tri[(size_t)u * 6];
+        for (int r = 0; r + 1 < cnt[u]; ++r) {
+            const int end = L.uid[vertex(t[r], 2)];
+            int q = r + 1;
+            while (q < cnt[u] && L.uid[vertex(t[q], 1)] != end) ++q;
+            if (q == cnt[u]) throw Error(TNG_E_INVAL, "mesh build: open ring of triangles");
+            std::swap(t[r + 1], t[q]);
+        }
+        if (cnt[u] < 5 || L.uid[vertex(t[cnt[u] - 1], 2)] != L.uid[vertex(t[0], 1)])
+            throw Error(TNG_E_INVAL, "mesh build: open ring of triangles");
+        for (int r = 0; r < 6; ++r) nb[(size_t)u * 6 + r] = vertex(t[r < cnt[u] ? r : 0], 1);
+    }
+    const size_t ns = (size_t)10 * m1 * m1;
+    std::vector<int> st(ns * 6), sn(ns * 6);
+    for (size_t q = 0; q < ns; ++q)
+        for (int r = 0; r < 6; ++r) {
+            st[q * 6 + r] = tri[(size_t)L.uid[q] * 6 + r];
+            sn[q * 6 + r] = nb[(size_t)L.uid[q] * 6 + r];
+        }
+    L.ring_tri.alloc(st.size());
+    L.ring_nb.alloc(sn.size());
+    TNG_HIP(hipMemcpy(L.ring_tri.p, st.data(), st.size() * sizeof(int), hipMemcpyHostToDevice));
+    TNG_HIP(hipMemcpy(L.ring_nb.p, sn.data(), sn.size() * sizeof(int), hipMemcpyHostToDevice));
+}
+
 void build_level(Level& L, int m, int n, double r_in, double r_out, bool device) {
     L.m = m;
     L.n = n;
@@ -120,26 +174,36 @@ void build_level(Level& L, int m, int n, double r_in, double r_out, bool device)
     }
     // duplicate groups: the same geometric node reached from several diamonds
     // is computed from the same parent pairs, so its coordinates agree exactly.
-    std::map<std::tuple<long long, long long, long long>, int> key2id;
-    std::vector<std::vector<int>> members;
+    // Only nodes on diamond edges are shared; ids are numbered by first appearance.
+    std::map<std::tuple<long long, long long, long long>, int> key2group;
+    std::vector<std::vector<int>> members;      // copies of every edge node, by first appearance
+    std::vector<int> group_of(10 * nl, -1);
     L.uid.resize(10 * nl);
+    int n_ids = 0;
     for (size_t q = 0; q < 10 * nl; ++q) {
+        const int i = (int)(q % nl) / (m + 1), j = (int)(q % nl) % (m + 1);
+        if (i != 0 && i != m && j != 0 && j != m) {
+            L.uid[q] = n_ids++;
+            continue;
+        }
         auto key = std::make_tuple(std::llround(L.unit[q * 3 + 0] * 1e11),
                                    std::llround(L.unit[q * 3 + 1] * 1e11),
                                    std::llround(L.unit[q * 3 + 2] * 1e11));
-        auto it = key2id.find(key);
-        int id;
-        if (it == key2id.end()) {
-            id = (int)members.size();
-            key2id.emplace(key, id);
+        auto it = key2group.find(key);
+        int g;
+        if (it == key2group.end()) {
+            g = (int)members.size();
+            key2group.emplace(key, g);
             members.emplace_back();
+            L.uid[q] = n_ids++;
         } else {
-            id = it->second;
+            g = it->second;
+            L.uid[q] = L.uid[members[g][0]];
         }
-        members[id].push_back((int)q);
-        L.uid[q] = id;
+        members[g].push_back((int)q);
+        group_of[q] = g;
     }
-    L.n_unique_lat = (int)members.size();
+    L.n_unique_lat = n_ids;
     if (L.n_unique_lat != 10 * m * m + 2)
         throw Error(TNG_E_INVAL, "mesh build: unexpected number of unique lateral nodes");
     L.grp_ptr_h.assign(1, 0);
@@ -220,6 +284,7 @@ void build_level(Level& L, int m, int n, double r_in, double r_out, bool device)
         L.lat_grp.alloc(lg.size());
         TNG_HIP(hipMemcpy(L.lat_grp.p, lg.data(), lg.size() * sizeof(int), hipMemcpyHostToDevice));
     }
+    build_rings(L);
     L.grp_ptr.alloc(L.grp_ptr_h.size());
     TNG_HIP(hipMemcpy(L.grp_ptr.p, L.grp_ptr_h.data(), L.grp_ptr_h.size() * sizeof(int), hipMemcpyHostToDevice));
     L.grp_slot.alloc(L.grp_slot_h.size());
@@ -229,7 +294,7 @@ void build_level(Level& L, int m, int n, double r_in, double r_out, bool device)
     std::vector<double> im(10 * nl);
     std::vector<float> im32(10 * nl);
     for (size_t q = 0; q < 10 * nl; ++q) {
-        im[q] = 1.0 / (double)members[L.uid[q]].size();
+        im[q] = group_of[q] < 0 ? 1.0 : 1.0 / (double)members[group_of[q]].size();
         im32[q] = (float)im[q];
     }
     L.inv_mult64.alloc(im.size());

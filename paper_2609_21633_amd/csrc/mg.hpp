@@ -46,9 +46,11 @@ void vec_rotation(const tng_ctx* ctx, const Level& L, int a, T* const out[3]);
 template <typename T>
 // twopt: the viscous block with the two-radial-point rule (hg_alpha must then be 0);
 // fs: free-slip spheres (bit 0 inner, bit 1 outer, the TNG_OP_FREESLIP_* bits >> 4),
-// whose rows get the isotropic projected diagonal trace(P A_jj P) / 2
+// whose rows get the isotropic projected diagonal trace(P A_jj P) / 2; invert: 1 / diagonal
 void mg_diag_A(const tng_ctx* ctx, const Level& L, const T* eta, double hg_alpha, T* const d[3], bool twopt = false,
-               unsigned fs = 0);
+               unsigned fs = 0, bool invert = false);
+// lateral slots per workgroup of the kernels that gather over a node's ring of triangles
+int ring_slots_per_block(const Level& L, int maxl);
 // x <- P x + N b at the free-slip layers fs (b == nullptr: b = 0)
 template <typename T>
 void vec_fs_project(const tng_ctx* ctx, const Level& L, unsigned fs, T* const x[3], const T* const b[3]);

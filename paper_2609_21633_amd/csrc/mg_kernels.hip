@@ -24,8 +24,6 @@ inline void check_counts(const SlotBatch& sb) {
         TNG_REQUIRE(sb.cnt[z] >= 1 && sb.cnt[z] <= MAX_MDOT, "per-slot vector count out of range");
 }
 
-__constant__ IsoWeights<double> c_isomg = make_iso_weights<double>();
-
 struct NodeIdx {
     int d, i, j, k;
 };
@@ -83,105 +81,213 @@ __device__ __forceinline__ double hg_eps(const double* g, double s1, double V, d
 // tangential diagonal entries are replaced by their mean, the same value in all three
 // components, so that D^{-1} maps tangential vectors to tangential vectors:
 // trace(P A_jj P) / 2 = sum_e V eta (|grad phi|^2 + (|grad phi|^2 - (rhat.grad phi)^2) / 6).
-// Per-diamond partial sums.
+// Rows of no-slip spheres are 1.  invert: the reciprocal of every entry.
+//
+// With a the lateral part of the basis gradient (grad phi = s1 a +- g3, s1 = 1/(2 r_m),
+// V = r_m^2 g9) an entry of a wedge is eta (A_c +- r_m B_c + r_m^2 C_c), + for the wedge
+// below the node and - for the one above, with nine values per triangle that do not
+// depend on the layer:
+//   A_c = g9/4 (|a|^2 + a_c^2/3), B_c = g9 (a.g3 + a_c g3_c/3), C_c = g9 (|g3|^2 + g3_c^2/3);
+// the two-point rule changes the radial factors only (sums over its points: 4/3,
+// r_m +- dr/6, r_m^2 + dr^2/12).  A workgroup takes nlb consecutive lateral slots, forms
+// their triangles' values once in LDS and then streams the slots' layers, 63 nodes per wave
+// and trip: a lane forms the six wedges above its node, for their bottom node (its own) and
+// their top node (handed to the lane above), so every viscosity is read once per lateral
+// node.  Every node gets its complete sum over the triangles of all diamonds (no interface
+// sum, no Dirichlet pass).  FP64 (128,128) with its two coarser levels: 0.33 ms, against
+// 1.51 ms (+ 0.08 ms of closing passes) for one thread per node gathering twelve wedges;
+// 0.19 ms is what reading eta and writing the diagonal once takes at the copy rate.
+constexpr int DIAG_MAXL = 16;   // lateral slots of a workgroup, at most
+
 template <typename T>
-__global__ void diag_A_kernel(const T* __restrict__ eta, const double* __restrict__ geo, int m, int n,
-                              double r_in, double dr, double hg_alpha, int twopt, int fs,
-                              const double* __restrict__ unit, T* d0, T* d1, T* d2, long long nslots) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nslots) return;
-    const NodeIdx q = decode_node(t, m, n);
-    const bool proj = ((fs & 1) && q.k == 0) || ((fs & 2) && q.k == n);
-    const double* rh = unit + 3 * ((((long long)q.d * (m + 1) + q.i) * (m + 1)) + q.j);
-    double acc[3] = {0, 0, 0};
-    for (int ci = q.i - 1; ci <= q.i; ++ci) {
-        if (ci < 0 || ci >= m) continue;
-        for (int cj = q.j - 1; cj <= q.j; ++cj) {
-            if (cj < 0 || cj >= m) continue;
-            const int di = q.i - ci, dj = q.j - cj;
-            const double* gcol = geo + (((long long)q.d * m + ci) * m + cj) * GEO_PER_COL;
-            for (int ck = q.k - 1; ck <= q.k; ++ck) {
-                if (ck < 0 || ck >= n) continue;
-                const int top = q.k - ck;
-                const double rm = r_in + (ck + 0.5) * dr;
-                const double s1 = 0.5 / rm;
-                for (int wd = 0; wd < 2; ++wd) {
-                    // local lateral index of the node in this wedge, -1 if not a vertex
-                    int lat = -1;
-                    if (wd == 0) lat = (di == 0 && dj == 0) ? 0 : (di == 1 && dj == 0) ? 1 : (di == 0 && dj == 1) ? 2 : -1;
-                    else lat = (di == 1 && dj == 1) ? 0 : (di == 0 && dj == 1) ? 1 : (di == 1 && dj == 0) ? 2 : -1;
-                    if (lat < 0) continue;
-                    const double* g = gcol + wd * GEO_PER_TRI;
-                    double gr[3];
-                    const double e = (double)eta[((((long long)q.d * m + ci) * m + cj) * n + ck) * 2 + wd];
-                    if (twopt) {
-                        for (int qq = 0; qq < 2; ++qq) {
-                            const double zq = qq == 0 ? -TWOPT_ZETA : TWOPT_ZETA;
-                            const double rq = rm + zq * (0.5 * dr);
-                            basis_grad_at(g, 0.5 / rq, zq, lat, top, gr);
-                            const double Vq = 0.5 * rq * rq * g[9];
-                            const double nn = gr[0] * gr[0] + gr[1] * gr[1] + gr[2] * gr[2];
-                            for (int c = 0; c < 3; ++c) acc[c] += Vq * e * (nn + gr[c] * gr[c] / 3.0);
-                        }
-                        continue;
-                    }
-                    basis_grad(g, s1, lat, top, gr);
-                    const double V = rm * rm * g[9];
-                    const double nn = gr[0] * gr[0] + gr[1] * gr[1] + gr[2] * gr[2];
-                    if (proj) {
-                        const double gn = rh[0] * gr[0] + rh[1] * gr[1] + rh[2] * gr[2];
-                        const double v = V * e * (nn + (nn - gn * gn) / 6.0);
-                        for (int c = 0; c < 3; ++c) acc[c] += v;
-                        continue;
-                    }
-                    const double hg = hg_alpha != 0.0 ? (2.0 / 3.0) * hg_eps(g, s1, V, e, hg_alpha) : 0.0;
-                    for (int c = 0; c < 3; ++c) acc[c] += V * e * (nn + gr[c] * gr[c] / 3.0) + hg;
-                }
-            }
+__global__ void __launch_bounds__(256) diag_A_kernel(const T* __restrict__ eta, const double* __restrict__ geo,
+                                                     const int* __restrict__ ring_tri, int nlat, int nlb, int n,
+                                                     MagicDiv dn1, double r_in, double dr, double hg_alpha, int twopt,
+                                                     int fs, const double* __restrict__ unit, int invert, T* d0, T* d1,
+                                                     T* d2) {
+    __shared__ double coef[DIAG_MAXL * 6][9];
+    __shared__ int code[DIAG_MAXL * 6];
+    const int lat0 = (int)xcd_block() * nlb;
+    if (lat0 >= nlat) return;
+    const int nl = min(nlb, nlat - lat0);
+    for (int x = threadIdx.x; x < nl * 6; x += 256) {
+        const int own = ring_tri[(size_t)lat0 * 6 + x];
+        // a vertex of five triangles: the sixth is the first one with zero values
+        const int cd = own >= 0 ? own : ring_tri[(size_t)lat0 * 6 + x - 5];
+        code[x] = cd;
+        const double* g = geo + (size_t)(cd >> 3) * GEO_PER_COL + ((cd >> 2) & 1) * GEO_PER_TRI;
+        const int lat = cd & 3;
+        const double g9 = own >= 0 ? g[9] : 0.0;
+        double a[3], aa = 0.0, ag = 0.0, gg = 0.0, as = 0.0;
+        for (int c = 0; c < 3; ++c) {
+            a[c] = lat == 0 ? -(g[c] + g[3 + c]) : (lat == 1 ? g[c] : g[3 + c]);
+            aa += a[c] * a[c];
+            ag += a[c] * g[6 + c];
+            gg += g[6 + c] * g[6 + c];
+            as += g[c] * g[c] + g[3 + c] * g[3 + c] + g[c] * g[3 + c];
+        }
+        // hourglass control: 2/3 eps_e, eps_e = alpha 5/27 eta V (4 s1^2 as + 6 gg)
+        const double h = hg_alpha * (10.0 / 81.0) * g9;
+        for (int c = 0; c < 3; ++c) {
+            coef[x][c] = 0.25 * g9 * (aa + a[c] * a[c] / 3.0) + h * as;
+            coef[x][3 + c] = g9 * (ag + a[c] * g[6 + c] / 3.0);
+            coef[x][6 + c] = g9 * (gg + g[6 + c] * g[6 + c] / 3.0) + h * 6.0 * gg;
         }
     }
-    d0[t] = T(acc[0]);
-    d1[t] = T(acc[1]);
-    d2[t] = T(acc[2]);
+    __syncthreads();
+    const int n1 = n + 1;
+    const size_t out0 = (size_t)lat0 * n1;
+    const int total = nl * n1, lane = threadIdx.x & 63;
+    const double q0 = twopt ? 4.0 / 3.0 : 1.0, q1 = twopt ? dr / 6.0 : 0.0, q2 = twopt ? dr * dr / 12.0 : 0.0;
+    // trip: nodes [t0 + 1, t0 + 64) of the workgroup's columns; lane 0 forms the node below
+    for (int t0 = 63 * (int)(threadIdx.x >> 6) - 1; t0 + 1 < total; t0 += 63 * 4) {
+        const int t = t0 + lane;
+        const unsigned tc = (unsigned)min(max(t, 0), total - 1);
+        const int li = (int)mdiv(tc, dn1), k = (int)tc - li * n1;
+        // the wedges above the node: p = sum eta (A + r^2 C), q = sum eta r B
+        const double rm = r_in + (k + 0.5) * dr, w1 = rm + q1, w1b = rm - q1, w2 = rm * rm + q2;
+        const int ka = min(k, n - 1);
+        T e[6];
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            const int cd = code[li * 6 + r];
+            e[r] = eta[((size_t)(cd >> 3) * n + ka) * 2 + ((cd >> 2) & 1)];
+        }
+        double p[3] = {0.0, 0.0, 0.0}, q[3] = {0.0, 0.0, 0.0}, s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            const double x = (double)e[r];
+            const double* cf = coef[li * 6 + r];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                p[c] += cf[c] * x;
+                q[c] += cf[3 + c] * x;
+                s[c] += cf[6 + c] * x;
+            }
+        }
+        double acc[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double m = q0 * p[c] + w2 * s[c];
+            const double top = lane_below(k < n && t >= 0 ? m + w1 * q[c] : 0.0);
+            acc[c] = (k < n ? m - w1b * q[c] : 0.0) + top;
+        }
+        if (lane == 0 || t >= total) continue;
+        if ((k == 0 && !(fs & 1)) || (k == n && !(fs & 2))) {
+            acc[0] = acc[1] = acc[2] = 1.0;
+        } else if (k == 0 || k == n) {
+            // free slip: the wedge below the outer sphere, or above the inner one
+            const bool top = k > 0;
+            const double rb = r_in + ((top ? k - 1 : k) + 0.5) * dr;
+            const double* rh = unit + 3 * (size_t)(lat0 + li);
+            acc[0] = 0.0;
+            for (int r = 0; r < 6; ++r) {
+                const int cd = ring_tri[(size_t)(lat0 + li) * 6 + r];
+                if (cd < 0) break;
+                const int cell = cd >> 3, wd = (cd >> 2) & 1;
+                const double* g = geo + (size_t)cell * GEO_PER_COL + wd * GEO_PER_TRI;
+                double gr[3];
+                basis_grad(g, 0.5 / rb, cd & 3, top ? 1 : 0, gr);
+                const double ev = (double)eta[((size_t)cell * n + (top ? k - 1 : k)) * 2 + wd];
+                const double nn = gr[0] * gr[0] + gr[1] * gr[1] + gr[2] * gr[2];
+                const double gn = rh[0] * gr[0] + rh[1] * gr[1] + rh[2] * gr[2];
+                acc[0] += rb * rb * g[9] * ev * (nn + (nn - gn * gn) / 6.0);
+            }
+            acc[1] = acc[2] = acc[0];
+        }
+        if (invert)
+            for (int c = 0; c < 3; ++c) acc[c] = (double)(T(1) / T(acc[c]));
+        d0[out0 + t] = T(acc[0]);
+        d1[out0 + t] = T(acc[1]);
+        d2[out0 + t] = T(acc[2]);
+    }
 }
 
 // Lumped M_{1/eta} on the pressure level: m_I = sum_e (V_e / eta_e) psi_I(q_c^e)
-// (eq:pmass, row-sum lumping, one-point rule), gathered per coarse node.
+// (eq:pmass, row-sum lumping, one-point rule), per-diamond partial sums.  A workgroup
+// owns PM_T x PM_T lateral coarse nodes and PM_K of their layers: first every coarse cell
+// around them reduces its sixteen wedges to eight corner values in LDS (one reciprocal
+// per wedge, at most 1.7 times per wedge over all workgroups), then every node adds its
+// eight cells in a fixed order.  FP64 (128,128): 0.114 ms (0.49 ms for one thread per
+// coarse node with its 128 wedges); reading eta once takes 0.065 ms at the copy rate.
+constexpr int PM_T = 4, PM_K = 16;
+
 template <typename T>
-__global__ void pmass_kernel(const T* __restrict__ eta, const double* __restrict__ geo, int m, int n,
-                             double r_in, double dr, T* __restrict__ out, long long ncslots) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ncslots) return;
+__global__ void __launch_bounds__(256) pmass_kernel(const T* __restrict__ eta, const double* __restrict__ geo, int m,
+                                                    int n, double r_in, double dr, T* __restrict__ out) {
+    constexpr int PC = PM_T + 1, PK = PM_K + 1;
+    constexpr IsoWeights<double> iso = make_iso_weights<double>();
+    __shared__ double part[8][PC * PC][PK];
     const int mc = m / 2, nc = n / 2;
-    const NodeIdx q = decode_node(t, mc, nc);
-    double acc = 0.0;
-    for (int Ic = q.i - 1; Ic <= q.i; ++Ic) {
-        if (Ic < 0 || Ic >= mc) continue;
-        for (int Jc = q.j - 1; Jc <= q.j; ++Jc) {
-            if (Jc < 0 || Jc >= mc) continue;
-            const int lc = (q.i - Ic) + 2 * (q.j - Jc);
-            for (int Kc = q.k - 1; Kc <= q.k; ++Kc) {
-                if (Kc < 0 || Kc >= nc) continue;
-                const int rc = q.k - Kc;
-                for (int a = 0; a < 2; ++a)
-                    for (int b = 0; b < 2; ++b) {
-                        const int ci = 2 * Ic + a, cj = 2 * Jc + b;
-                        const double* gcol = geo + (((long long)q.d * m + ci) * m + cj) * GEO_PER_COL;
-                        for (int c = 0; c < 2; ++c) {
-                            const int ck = 2 * Kc + c;
-                            const double rm = r_in + (ck + 0.5) * dr;
-                            const double rw = c_isomg.rw[c][rc];
-                            for (int wd = 0; wd < 2; ++wd) {
-                                const double V = rm * rm * gcol[wd * GEO_PER_TRI + 9];
-                                const double e = (double)eta[((((long long)q.d * m + ci) * m + cj) * n + ck) * 2 + wd];
-                                acc += V / e * c_isomg.lw[a][b][wd][lc] * rw;
+    const int nt = (mc + PM_T) / PM_T, nkt = (nc + PM_K) / PM_K;   // tiles over mc + 1 nodes, nc + 1 layers
+    int b = (int)xcd_block();
+    const int K0 = (b % nkt) * PM_K;
+    b /= nkt;
+    const int J0 = (b % nt) * PM_T;
+    b /= nt;
+    const int I0 = (b % nt) * PM_T, d = b / nt;
+    for (int x = threadIdx.x; x < PC * PC * PK; x += 256) {
+        const int lk = x % PK, lj = (x / PK) % PC, li = x / (PK * PC);
+        const int I = I0 - 1 + li, J = J0 - 1 + lj, K = K0 - 1 + lk;
+        double p[4][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+        if (I >= 0 && I < mc && J >= 0 && J < mc && K >= 0 && K < nc) {
+            const double r0 = r_in + (2 * K + 0.5) * dr, r1 = r0 + dr;
+            T e[2][2][4];
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int bb = 0; bb < 2; ++bb) {
+                    const size_t col = ((size_t)d * m + 2 * I + a) * m + 2 * J + bb;
+                    const T* ep = eta + (col * n + 2 * K) * 2;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) e[a][bb][q] = ep[q];
+                }
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int bb = 0; bb < 2; ++bb) {
+                    const double* g = geo + (((size_t)d * m + 2 * I + a) * m + 2 * J + bb) * GEO_PER_COL;
+#pragma unroll
+                    for (int wd = 0; wd < 2; ++wd) {
+                        const double g9 = g[wd * GEO_PER_TRI + 9];
+                        const double v0 = r0 * r0 * g9 / (double)e[a][bb][wd];
+                        const double v1 = r1 * r1 * g9 / (double)e[a][bb][2 + wd];
+                        const double bot = iso.rw[0][0] * v0 + iso.rw[1][0] * v1;
+                        const double top = iso.rw[0][1] * v0 + iso.rw[1][1] * v1;
+#pragma unroll
+                        for (int lc = 0; lc < 4; ++lc) {
+                            const double w = iso.lw[a][bb][wd][lc];
+                            if (w != 0.0) {
+                                p[lc][0] += w * bot;
+                                p[lc][1] += w * top;
                             }
                         }
                     }
-            }
+                }
+        }
+#pragma unroll
+        for (int lc = 0; lc < 4; ++lc) {
+            part[lc][li * PC + lj][lk] = p[lc][0];
+            part[4 + lc][li * PC + lj][lk] = p[lc][1];
         }
     }
-    out[t] = T(acc);
+    __syncthreads();
+    for (int x = threadIdx.x; x < PM_T * PM_T * PM_K; x += 256) {
+        const int lk = x % PM_K, lj = (x / PM_K) % PM_T, li = x / (PM_K * PM_T);
+        const int I = I0 + li, J = J0 + lj, K = K0 + lk;
+        if (I > mc || J > mc || K > nc) continue;
+        double acc = 0.0;
+        // the cells on either side of the node; its corner in them, and the face (1: the
+        // cell below has it on its top)
+#pragma unroll
+        for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+            for (int cj = 0; cj < 2; ++cj)
+#pragma unroll
+                for (int ck = 0; ck < 2; ++ck)
+                    acc += part[(1 - ci) + 2 * (1 - cj) + 4 * (1 - ck)][(li + ci) * PC + lj + cj][lk + ck];
+        out[(((size_t)d * (mc + 1) + I) * (mc + 1) + J) * (nc + 1) + K] = T(acc);
+    }
 }
 
 // Prolongation (W1 interpolation in index space): a fine node that is a
@@ -405,19 +511,6 @@ __global__ void invert_kernel(long long n, T* a) {
     if (t < n) a[t] = T(1) / a[t];
 }
 
-// Dirichlet (no-slip) rows of a velocity diagonal are identity rows; fs: free-slip
-// spheres (bit 0 inner, bit 1 outer), whose rows keep their diagonal.
-template <typename T>
-__global__ void diag_dirichlet_kernel(long long ncol, int n, int fs, T* d0, T* d1, T* d2) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 2 * ncol) return;
-    if ((t & 1) ? (fs & 2) : (fs & 1)) return;
-    const long long idx = (t >> 1) * (n + 1) + ((t & 1) ? n : 0);
-    d0[idx] = T(1);
-    d1[idx] = T(1);
-    d2[idx] = T(1);
-}
-
 // Free-slip boundary rows of an iterate: x <- P x + N b = x + (rhat.b - rhat.x) rhat at
 // the layers of the free-slip spheres (fs bit 0 inner, bit 1 outer), b == nullptr: b = 0.
 // The normal rows of P A P + N are identity rows, so this solves them exactly and leaves
@@ -543,21 +636,6 @@ __global__ void __launch_bounds__(256) axpby_kernel(long long n, T a, const T* _
 // pointers are read once per block into scalar registers, and every load of
 // an element is issued before the first use.
 constexpr int DOT_BS = 256;
-
-struct MagicDiv {
-    unsigned mul;   // ceil(2^(32 + sh) / d) - 2^32
-    int sh;         // ceil(log2 d)
-};
-inline MagicDiv magic_div(unsigned d) {
-    MagicDiv m{0u, 0};
-    while ((1ull << m.sh) < d) ++m.sh;
-    const unsigned long long big = 1ull << (32 + m.sh);
-    m.mul = (unsigned)((big + d - 1) / d - (1ull << 32));
-    return m;
-}
-__device__ __forceinline__ unsigned mdiv(unsigned t, MagicDiv m) {
-    return (unsigned)((((unsigned long long)__umulhi(t, m.mul)) + t) >> m.sh);
-}
 
 // Residual r = b - A_D x from a raw viscous apply y (the closing pass fused as in
 // cheb_post_update_kernel: copies summed in group order, identity rows r = b - x).
@@ -1429,27 +1507,33 @@ __global__ void coarse_assemble_kernel(int nd, const int* __restrict__ copy_ptr,
 // launchers
 // ---------------------------------------------------------------------------
 
+// Lateral slots per workgroup of a kernel that streams whole columns with per-column data
+// in LDS: about 2048 nodes a workgroup, fewer on small levels (at least 512 workgroups, as
+// long as 256 nodes a workgroup are left), at most maxl.
+int ring_slots_per_block(const Level& L, int maxl) {
+    const int n1 = L.n + 1;
+    int nlb = std::max(1, std::min(maxl, 2048 / n1));
+    while (nlb > 1 && L.lat_slots() < 512LL * nlb && nlb * n1 > 256) nlb = (nlb + 1) / 2;
+    return nlb;
+}
+
 template <typename T>
 void mg_diag_A(const tng_ctx* ctx, const Level& L, const T* eta, double hg_alpha, T* const d[3], bool twopt,
-               unsigned fs) {
+               unsigned fs, bool invert) {
     require_unbatched("mg_diag_A");
-    const long long ns = L.node_slots();
-    diag_A_kernel<T><<<nblk(ns, 256), 256, 0, ctx->stream>>>(eta, L.geo64.p, L.m, L.n, L.r_in, L.dr(),
-                                                             hg_alpha, twopt ? 1 : 0, (int)fs, L.unit64.p,
-                                                             d[0], d[1], d[2], ns);
-    TNG_HIP(hipGetLastError());
-    void* f[3] = {d[0], d[1], d[2]};
-    launch_interface(ctx, L, prec_of<T>(), 0, 3, f);
-    diag_dirichlet_kernel<T><<<nblk(2 * L.lat_slots(), 256), 256, 0, ctx->stream>>>(L.lat_slots(), L.n, (int)fs,
-                                                                                  d[0], d[1], d[2]);
+    const int nlb = ring_slots_per_block(L, DIAG_MAXL);
+    diag_A_kernel<T><<<nblk(L.lat_slots(), nlb), 256, 0, ctx->stream>>>(
+        eta, L.geo64.p, L.ring_tri.p, (int)L.lat_slots(), nlb, L.n, magic_div((unsigned)(L.n + 1)), L.r_in, L.dr(),
+        hg_alpha, twopt ? 1 : 0, (int)fs, L.unit64.p, invert ? 1 : 0, d[0], d[1], d[2]);
     TNG_HIP(hipGetLastError());
 }
 
 template <typename T>
 void mg_pmass(const tng_ctx* ctx, const Level& L, const Level& Lp, const T* eta, T* mdiag) {
     require_unbatched("mg_pmass");
-    const long long ns = Lp.node_slots();
-    pmass_kernel<T><<<nblk(ns, 256), 256, 0, ctx->stream>>>(eta, L.geo64.p, L.m, L.n, L.r_in, L.dr(), mdiag, ns);
+    const long long nt = (Lp.m + PM_T) / PM_T, nkt = (Lp.n + PM_K) / PM_K;
+    pmass_kernel<T><<<(unsigned)(10 * nt * nt * nkt), 256, 0, ctx->stream>>>(eta, L.geo64.p, L.m, L.n, L.r_in, L.dr(),
+                                                                             mdiag);
     TNG_HIP(hipGetLastError());
     void* f[1] = {mdiag};
     launch_interface(ctx, Lp, prec_of<T>(), 0, 1, f);
@@ -1823,7 +1907,7 @@ void vec_schur(const tng_ctx* ctx, long long n, const T* r, const T* mdiag, T* z
 }
 
 #define TNG_INST(T)                                                                                        \
-    template void mg_diag_A<T>(const tng_ctx*, const Level&, const T*, double, T* const[3], bool, unsigned);      \
+    template void mg_diag_A<T>(const tng_ctx*, const Level&, const T*, double, T* const[3], bool, unsigned, bool); \
     template void vec_fs_project<T>(const tng_ctx*, const Level&, unsigned, T* const[3], const T* const[3]);      \
     template void vec_rotation<T>(const tng_ctx*, const Level&, int, T* const[3]);                                \
     template void mg_pmass<T>(const tng_ctx*, const Level&, const Level&, const T*, T*);                  \

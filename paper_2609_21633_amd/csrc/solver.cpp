@@ -685,8 +685,7 @@ void setup_level_operators(tng_solver* s) {
     for (int l = 0; l < s->nlev - 1; ++l) {
         MGLevel<T>& M = H[l];
         T* d[3] = {M.invd.p, M.invd.p + M.ns, M.invd.p + 2 * M.ns};
-        mg_diag_A<T>(s->ctx, *M.L, M.eta.p, s->opts.hg_alpha, d, twopt_flag(s) != 0, fs_bits(s));
-        vec_invert<T>(s->ctx, 3 * M.ns, M.invd.p);
+        mg_diag_A<T>(s->ctx, *M.L, M.eta.p, s->opts.hg_alpha, d, twopt_flag(s) != 0, fs_bits(s), true);
         M.lmax = power_lmax<T>(s, l);
         M.cheb_h = chebyshev_coefficients(std::max(1, s->opts.cheb_degree), s->opts.cheb_lo * M.lmax,
                                           s->opts.cheb_hi * M.lmax);

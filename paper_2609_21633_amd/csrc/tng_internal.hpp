@@ -204,6 +204,7 @@ struct Level {
     DevBuf<float> eg32;
     DevBuf<int> grp_ptr, grp_slot;    // duplicate groups (CSR over lateral slots)
     DevBuf<int> lat_grp;              // [10][m+1][m+1]: the slot's duplicate group, -1 for none
+    DevBuf<int> ring_tri, ring_nb;    // [10][m+1][m+1][6]: triangles and neighbours around a node (mesh.cpp)
     DevBuf<uint8_t> owner;            // [10][m+1][m+1]: 1 for the first copy of a node
     DevBuf<double> inv_mult64;        // [10][m+1][m+1]: 1 / number of copies of the node
     DevBuf<double> unit64;            // [10][m+1][m+1][3] unit vectors

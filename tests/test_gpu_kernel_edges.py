@@ -1,0 +1,77 @@
+"""GPU parity of the kernels that gather over a node's ring of triangles and of the small
+fused kernels of the solver, at the edges of their decompositions: the smallest shells
+(every node next to a five-ring vertex), radial counts around the tiles and the workgroup
+sizes, and the largest radial counts of the streamed kernels."""
+import numpy as np
+import pytest
+
+import synthetic
+from oracle.mesh import ShellMesh
+from oracle.solver_ref import lumped_pressure_mass
+from oracle.stokes import StokesOracle, buoyancy_rhs
+from tests._support import LayoutMap
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tng():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_21633_amd as t
+    return t
+
+
+@pytest.fixture(scope="module")
+def ctx(tng):
+    return tng.Context(0)
+
+
+_cache = {}
+
+
+def shell(tng, ctx, mt, nr, levels=2):
+    """(mesh, oracle meshes, layout maps, viscosity, oracle) of one (mt, nr) shell."""
+    if (mt, nr) not in _cache:
+        mesh = tng.Mesh(ctx, mt, nr, levels=levels)
+        om = ShellMesh(mt, nr)
+        omp = ShellMesh(mt // 2, nr // 2, hierarchy=om.h)
+        lm, lmp = LayoutMap(*mesh.coords(0), om), LayoutMap(*mesh.coords(1), omp)
+        eta, _, _ = synthetic.uniform_operator_inputs(om.n_wedges, om.n_nodes, omp.n_nodes, 3)
+        _cache[(mt, nr)] = (mesh, om, omp, lm, lmp, eta, StokesOracle(mt, nr, eta, hierarchy=om.h))
+    return _cache[(mt, nr)]
+
+
+# one radial cell pair; layers around the pressure-mass tile (16 coarse layers) and the
+# 256 threads of a workgroup; several workgroups per level
+RING_SHELLS = [(2, 2), (4, 30), (4, 34), (2, 258), (8, 62)]
+
+
+@pytest.mark.parametrize("dtype,tol", [("float64", 1e-12), ("float32", 1e-6)])
+@pytest.mark.parametrize("mt,nr", RING_SHELLS)
+def test_diagonal_pressure_mass_buoyancy(tng, ctx, dtype, tol, mt, nr):
+    """Sums of at most twelve (diagonal) or 128 (mass) positive terms formed in FP64: element-
+    wise within 1e-12, in FP32 the rounding of the inputs and of the stored value (below
+    1e-6).  The buoyancy cancels between wedges: held to the largest entry."""
+    import torch
+    dt = getattr(torch, dtype)
+    mesh, om, omp, lm, lmp, eta, orc = shell(tng, ctx, mt, nr)
+    eta_t = torch.tensor(eta[lm.wedge_index()], device="cuda").to(dt)
+    d = torch.full((3,) + mesh.shape(0), float("nan"), dtype=dt, device="cuda")
+    tng.diag_A(ctx, mesh, 0, eta_t, d)
+    pm = torch.full(mesh.shape(1), float("nan"), dtype=dt, device="cuda")
+    tng.pressure_mass(ctx, mesh, 0, eta_t, pm)
+    T = synthetic.temperature(om.s, om.r, seed=3).ravel()
+    f = torch.full((3,) + mesh.shape(0), float("nan"), dtype=dt, device="cuda")
+    tng.rhs_buoyancy(ctx, mesh, 0, torch.tensor(lm.to_lib(T), device="cuda").to(dt), 1e5, f)
+    torch.cuda.synchronize()
+    want_d, want_m = orc.diag_A(), lumped_pressure_mass(orc, eta)
+    want_f = buoyancy_rhs(om, T, 1e5)
+    want_f[om.boundary_nodes()] = 0.0
+    got_d = lm.from_lib(d.double().cpu().numpy(), check_dups=1e-15)
+    got_m = lmp.from_lib(pm.double().cpu().numpy(), check_dups=1e-15)
+    got_f = lm.from_lib(f.double().cpu().numpy(), check_dups=1e-15)
+    assert (np.abs(got_d - want_d) <= tol * np.abs(want_d)).all()
+    assert (np.abs(got_m - want_m) <= tol * np.abs(want_m)).all()
+    assert np.abs(got_f - want_f).max() <= 10 * tol * np.abs(want_f).max()
