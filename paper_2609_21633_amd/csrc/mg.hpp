@@ -12,6 +12,7 @@ namespace tng {
 constexpr int MAX_MDOT = 24;          // vectors in one multi-dot / multi-axpy
 constexpr int DOT_BLOCKS = 4096;      // partial sums of a reduction (enough waves to fill HBM)
 constexpr int MAX_COARSE_DOF = 1024;  // dense coarsest-level solve
+constexpr int INV_NB = 32;            // pivot block of its inversion
 
 template <typename T>
 constexpr tng_prec prec_of() {
@@ -30,10 +31,13 @@ struct CoarseDense {
     long long nslots = 0;
     DevBuf<int> dof_slot;   // [ndof]: (owner slot << 2) | component
     DevBuf<int> slot_dof;   // [3][nslots]: DoF of every copy, -1 on Dirichlet rows
-    DevBuf<int> copy_ptr;   // [ndof + 1]: copies of each DoF (CSR)
-    DevBuf<int> copy_slot;  //   (slot << 2) | component of every copy
     DevBuf<double> Ainv;    // ndof x ndof
+    DevBuf<double> Awork;   // ndof x ndof, the other buffer of the inversion
     DevBuf<double> rotq;    // [3][ndof] orthonormal rigid rotations + sigma (free slip on both spheres)
+    // pivot blocks of the inversion, one launch each between the two buffers; the matrix
+    // is assembled where the last one leaves the inverse in Ainv
+    int inv_steps() const { return (ndof + INV_NB - 1) / INV_NB; }
+    double* matrix() { return inv_steps() % 2 ? Awork.p : Ainv.p; }
 };
 
 // free slip on both spheres: A <- A + sigma Q Q^T over the coarsest DoFs, Q the
@@ -93,10 +97,6 @@ void vec_mul(const tng_ctx* ctx, long long n, const T* a, const T* b, T* c);
 template <typename T>
 void vec_maxpy(const tng_ctx* ctx, long long n, const double* coef_dev, double sign, const T* const* vs_dev,
                int nq, T* y);
-template <typename T>
-void coarse_unit(const tng_ctx* ctx, const CoarseDense& cd, int col, T* const x[3]);
-template <typename T>
-void coarse_gather(const tng_ctx* ctx, const CoarseDense& cd, int col, const T* const y[3], double* Ad);
 void coarse_invert(const tng_ctx* ctx, CoarseDense& cd);
 template <typename T>
 void coarse_solve(const tng_ctx* ctx, const CoarseDense& cd, const T* const b[3], T* const x[3]);
@@ -130,7 +130,7 @@ void vec_tab_copy(const tng_ctx* ctx, long long n, const T* src, const T* const*
 void scal_gather(const tng_ctx* ctx, const double* src, int k, double* staging);
 void scal_scatter(const tng_ctx* ctx, const double* staging, int k, double* dst);
 template <typename T>
-void coarse_assemble(const tng_ctx* ctx, const CoarseDense& cd, const Level& L, const T* eta, double hg_alpha,
+void coarse_assemble(const tng_ctx* ctx, CoarseDense& cd, const Level& L, const T* eta, double hg_alpha,
                      bool twopt = false, unsigned fs = 0);
 
 struct EnergyWS;

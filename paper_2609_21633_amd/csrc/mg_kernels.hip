@@ -926,46 +926,86 @@ __global__ void __launch_bounds__(256) mdot_final_kernel(int nblocks, int nq, co
 
 // Dense coarsest level ------------------------------------------------------
 
-// Column `col` of the assembled coarsest operator restricted to unique
-// interior DoFs: y = A e_col has been computed in the slot layout; gather the
-// owner copies into row-major dense storage (A is symmetric).
-template <typename T>
-__global__ void coarse_gather_col_kernel(int ndof, const int* __restrict__ dof_slot, const T* __restrict__ y0,
-                                         const T* __restrict__ y1, const T* __restrict__ y2, int col,
-                                         double* __restrict__ Ad) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= ndof) return;
-    const int s = dof_slot[r];
-    const int c = s & 3;
-    const long long slot = s >> 2;
-    const T v = c == 0 ? y0[slot] : (c == 1 ? y1[slot] : y2[slot]);
-    Ad[(long long)col * ndof + r] = (double)v;
-}
-
-// Gauss-Jordan inversion of an SPD matrix in one workgroup (no pivoting is
-// needed for SPD matrices).  a: ndof x ndof, overwritten by its inverse.
-__global__ void __launch_bounds__(1024) gauss_jordan_kernel(int nd, double* a) {
-    __shared__ double prow[MAX_COARSE_DOF];
-    __shared__ double pcol[MAX_COARSE_DOF];
-    for (int p = 0; p < nd; ++p) {
+// One step of the blocked Gauss-Jordan inversion of an SPD matrix (no pivoting is needed):
+// with P the pivot block of INV_NB rows and columns and D = A_PP^{-1},
+//   A_PP <- D, A_Pj <- D A_Pj, A_iP <- -A_iP D, A_ij <- A_ij - A_iP D A_Pj.
+// Workgroup (bi, bj) writes block (i, j) of `out` from `in` (two buffers, so that no
+// workgroup waits for another) and inverts A_PP itself, in LDS.  Bound by the latency of
+// the INV_NB pivots of that inversion (the products are 32^3): one launch per pivot block
+// instead of one workgroup walking the whole matrix once per pivot (126 unknowns: four
+// launches of 24 us, 0.68 ms before).
+__global__ void __launch_bounds__(256) invert_step_kernel(int nd, int pb, const double* __restrict__ in,
+                                                          double* __restrict__ out) {
+    static_assert(INV_NB == 32, "256 threads hold a 32 x 32 block, four rows each");
+    __shared__ double D[INV_NB][INV_NB + 1], L[INV_NB][INV_NB + 1], R[INV_NB][INV_NB + 1];
+    __shared__ double prow[2][INV_NB], pcol[2][INV_NB];
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int p0 = pb * INV_NB, i0 = blockIdx.y * INV_NB, j0 = blockIdx.x * INV_NB;
+    // rows and columns past the matrix: identity in the pivot block, zero elsewhere
+    auto at = [&](int r, int c, double pad) {
+        return r < nd && c < nd ? in[(size_t)r * nd + c] : pad;
+    };
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = ty + 8 * q;
+        v[q] = at(p0 + r, p0 + tx, r == tx ? 1.0 : 0.0);
+        L[r][tx] = at(i0 + r, p0 + tx, 0.0);
+        R[r][tx] = at(p0 + r, j0 + tx, 0.0);
+        if (r == 0) prow[0][tx] = v[q];
+        if (tx == 0) pcol[0][r] = v[q];
+    }
+    // scalar Gauss-Jordan on the pivot block held in registers (row ty + 8 q, column tx);
+    // the next pivot's row and column are handed on through LDS, one barrier per pivot
+    for (int p = 0; p < INV_NB; ++p) {
         __syncthreads();
-        const double piv = a[(long long)p * nd + p];
-        for (int x = threadIdx.x; x < nd; x += blockDim.x) {
-            prow[x] = a[(long long)p * nd + x];
-            pcol[x] = a[(long long)x * nd + p];
+        const double* pr = prow[p & 1];
+        const double* pc = pcol[p & 1];
+        const double ip = 1.0 / pr[p], prx = pr[tx];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = ty + 8 * q;
+            const double f = pc[r] * ip;
+            if (r == p)
+                v[q] = tx == p ? ip : prx * ip;
+            else
+                v[q] = tx == p ? -f : v[q] - f * prx;
+            if (r == p + 1) prow[(p + 1) & 1][tx] = v[q];
+            if (tx == p + 1) pcol[(p + 1) & 1][r] = v[q];
         }
-        __syncthreads();
-        const double ip = 1.0 / piv;
-        const long long total = (long long)nd * nd;
-        for (long long e = threadIdx.x; e < total; e += blockDim.x) {
-            const int r = (int)(e / nd), c = (int)(e % nd);
-            double v;
-            if (r == p && c == p) v = ip;
-            else if (r == p) v = prow[c] * ip;
-            else if (c == p) v = -pcol[r] * ip;
-            else v = a[e] - pcol[r] * prow[c] * ip;
-            a[e] = v;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) D[ty + 8 * q][tx] = v[q];
+    __syncthreads();
+    const bool pi = i0 == p0, pj = j0 == p0;
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    if (pi && pj) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t[q] = v[q];
+    } else if (pj) {
+        for (int k = 0; k < INV_NB; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[q] -= L[ty + 8 * q][k] * D[k][tx];
+    } else {
+        for (int k = 0; k < INV_NB; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[q] += D[ty + 8 * q][k] * R[k][tx];
+        if (!pi) {
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) R[ty + 8 * q][tx] = t[q];
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[q] = at(i0 + ty + 8 * q, j0 + tx, 0.0);
+            for (int k = 0; k < INV_NB; ++k)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) t[q] -= L[ty + 8 * q][k] * R[k][tx];
         }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = i0 + ty + 8 * q, c = j0 + tx;
+        if (r < nd && c < nd) out[(size_t)r * nd + c] = t[q];
     }
 }
 
@@ -989,8 +1029,10 @@ __global__ void __launch_bounds__(1024) coarse_solve_kernel(int nd, const int* _
     x0 = at_slot(x0, so);
     x1 = at_slot(x1, so);
     x2 = at_slot(x2, so);
+    // the columns are split among the G groups of nd threads that the workgroup holds, their
+    // sums added in group order (126 unknowns, eight groups: 13 -> 6.7 us a solve)
     __shared__ double rhs[MAX_COARSE_DOF];
-    __shared__ double sol[MAX_COARSE_DOF];
+    __shared__ double sol[MAX_COARSE_DOF];      // [G][nd], G nd <= 1024
     for (int r = threadIdx.x; r < nd; r += blockDim.x) {
         const int s = dof_slot[r];
         const int c = s & 3;
@@ -998,11 +1040,20 @@ __global__ void __launch_bounds__(1024) coarse_solve_kernel(int nd, const int* _
         rhs[r] = (double)(c == 0 ? b0[slot] : (c == 1 ? b1[slot] : b2[slot]));
     }
     __syncthreads();
-    for (int r = threadIdx.x; r < nd; r += blockDim.x) {
+    const int G = (int)blockDim.x / nd, grp = (int)threadIdx.x / nd, row = (int)threadIdx.x % nd;
+    if (grp < G) {
+        const int c0 = nd * grp / G, c1 = nd * (grp + 1) / G;
         double v = 0.0;
-        for (int c = 0; c < nd; ++c) v += Ainv[(long long)c * nd + r] * rhs[c];
-        sol[r] = v;
+#pragma unroll 8
+        for (int c = c0; c < c1; ++c) v += Ainv[(long long)c * nd + row] * rhs[c];
+        sol[grp * nd + row] = v;
     }
+    __syncthreads();
+    double sum = 0.0;
+    if ((int)threadIdx.x < nd)
+        for (int g = 0; g < G; ++g) sum += sol[g * nd + threadIdx.x];
+    __syncthreads();
+    if ((int)threadIdx.x < nd) sol[threadIdx.x] = sum;
     __syncthreads();
     for (long long t = threadIdx.x; t < 3 * nslots; t += blockDim.x) {
         const int c = (int)(t / nslots);
@@ -1013,19 +1064,6 @@ __global__ void __launch_bounds__(1024) coarse_solve_kernel(int nd, const int* _
         else if (c == 1) x1[slot] = v;
         else x2[slot] = v;
     }
-}
-
-template <typename T>
-__global__ void unit_vector_kernel(long long nslots, const int* __restrict__ slot_dof, int col, T* x0, T* x1,
-                                   T* x2) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 3 * nslots) return;
-    const int c = (int)(t / nslots);
-    const long long slot = t % nslots;
-    const T v = slot_dof[c * nslots + slot] == col ? T(1) : T(0);
-    if (c == 0) x0[slot] = v;
-    else if (c == 1) x1[slot] = v;
-    else x2[slot] = v;
 }
 
 // Pressure: zero nodal mean projection helper  p <- p - mean
@@ -1382,123 +1420,93 @@ __global__ void scal_scatter_kernel(const double* __restrict__ src, int k, doubl
     for (int i = threadIdx.x; i < k; i += blockDim.x) dst[i] = src[(long long)blockIdx.z * k + i];
 }
 
-// Column `col` of D A D on the coarsest level, assembled from the one-point
-// element matrices (eq:elemmat) of every wedge around every copy of the
-// column's node; one thread per column, fixed loop order.
+// Entry (row, col) of D A D on the coarsest level, one thread each: the one-point (or
+// two-point) element matrices (eq:elemmat) of the wedges around the column's node that
+// hold the row's node, in ring order.  With free slip the entry is that of P A P + N,
+// P = I - rhat rhat^T at either node on a free-slip sphere: the 3 x 3 block of the two
+// nodes is summed first.  126 unknowns: 14 us (0.23 ms with one thread per column).
 template <typename T>
-__global__ void coarse_assemble_kernel(int nd, const int* __restrict__ copy_ptr, const int* __restrict__ copy_slot,
-                                       const int* __restrict__ slot_dof, long long nslots, const T* __restrict__ eta,
-                                       const double* __restrict__ geo, int m, int n, double r_in, double dr,
-                                       double hg_alpha, int twopt, int fs, const double* __restrict__ unit,
-                                       double* __restrict__ Ad) {
-    const int col = blockIdx.x * blockDim.x + threadIdx.x;
-    if (col >= nd) return;
-    for (int r = 0; r < nd; ++r) Ad[(long long)col * nd + r] = 0.0;
+__global__ void __launch_bounds__(64) coarse_assemble_kernel(int nd, const int* __restrict__ dof_slot,
+                                                             const int* __restrict__ slot_dof, long long nslots,
+                                                             const int* __restrict__ ring_tri,
+                                                             const int* __restrict__ ring_nb,
+                                                             const T* __restrict__ eta, const double* __restrict__ geo,
+                                                             int m, int n, double r_in, double dr, double hg_alpha,
+                                                             int twopt, int fs, const double* __restrict__ unit,
+                                                             double* __restrict__ Ad) {
+    const int row = blockIdx.x * 64 + threadIdx.x, col = blockIdx.y;
+    if (row >= nd) return;
     auto on_fs = [&](int k) { return ((fs & 1) && k == 0) || ((fs & 2) && k == n); };
-    for (int cp = copy_ptr[col]; cp < copy_ptr[col + 1]; ++cp) {
-        const int sc = copy_slot[cp];
-        const long long slot = sc >> 2;
-        const int ccomp = sc & 3;
-        const NodeIdx q = decode_node(slot, m, n);
-        // free slip: the column is (P A P) e_c, P = I - rhat rhat^T at the column node and
-        // at every row node on a free-slip sphere
-        const bool pc = on_fs(q.k);
-        const double* nc = unit + 3 * ((((long long)q.d * (m + 1) + q.i) * (m + 1)) + q.j);
-        for (int ci = q.i - 1; ci <= q.i; ++ci) {
-            if (ci < 0 || ci >= m) continue;
-            for (int cj = q.j - 1; cj <= q.j; ++cj) {
-                if (cj < 0 || cj >= m) continue;
-                const int di = q.i - ci, dj = q.j - cj;
-                const double* gcol = geo + (((long long)q.d * m + ci) * m + cj) * GEO_PER_COL;
-                for (int ck = q.k - 1; ck <= q.k; ++ck) {
-                    if (ck < 0 || ck >= n) continue;
-                    const int top = q.k - ck;
-                    const double rm = r_in + (ck + 0.5) * dr;
-                    const double s1 = 0.5 / rm;
-                    for (int wd = 0; wd < 2; ++wd) {
-                        const int cdi[2][3] = {{0, 1, 0}, {1, 0, 1}};
-                        const int cdj[2][3] = {{0, 0, 1}, {1, 1, 0}};
-                        int lat = -1;
-                        for (int l = 0; l < 3; ++l)
-                            if (cdi[wd][l] == di && cdj[wd][l] == dj) lat = l;
-                        if (lat < 0) continue;
-                        const double* g = gcol + wd * GEO_PER_TRI;
-                        const double e = (double)eta[((((long long)q.d * m + ci) * m + cj) * n + ck) * 2 + wd];
-                        // quadrature points: q_c (weight 1), or the two radial points
-                        const int nq = twopt ? 2 : 1;
-                        for (int qq = 0; qq < nq; ++qq) {
-                            const double zq = twopt ? (qq == 0 ? -TWOPT_ZETA : TWOPT_ZETA) : 0.0;
-                            const double rq = twopt ? rm + zq * (0.5 * dr) : rm;
-                            const double V = (twopt ? 0.5 : 1.0) * rq * rq * g[9];
-                            double gj[3];
-                            if (twopt)
-                                basis_grad_at(g, 0.5 / rq, zq, lat, top, gj);
-                            else
-                                basis_grad(g, s1, lat, top, gj);
-                            const double eps = hg_alpha != 0.0 ? hg_eps(g, s1, V, e, hg_alpha) : 0.0;
-                            for (int l2 = 0; l2 < 6; ++l2) {
-                                const int lat2 = l2 % 3, top2 = l2 / 3;
-                                double gl[3];
-                                if (twopt)
-                                    basis_grad_at(g, 0.5 / rq, zq, lat2, top2, gl);
-                                else
-                                    basis_grad(g, s1, lat2, top2, gl);
-                                const long long s2 = (((long long)q.d * (m + 1) + ci + cdi[wd][lat2]) * (m + 1) +
-                                                      cj + cdj[wd][lat2]) * (n + 1) + ck + top2;
-                                const double gg = gj[0] * gl[0] + gj[1] * gl[1] + gj[2] * gl[2];
-                                // (A_e)_{(j,c),(l,d)} = V eta [delta_cd g_j.g_l + (g_j)_d (g_l)_c
-                                //                              - 2/3 (g_j)_c (g_l)_d]
-                                // hourglass term: eps delta_cd zeta_j zeta_l (delta_{lat_j, lat_l} - 1/3)
-                                auto entry = [&](int d2, int cc) {
-                                    double v = V * e * ((cc == d2 ? gg : 0.0) + gj[d2] * gl[cc] -
-                                                        (2.0 / 3.0) * gj[cc] * gl[d2]);
-                                    if (cc == d2)
-                                        v += eps * (top ? 1.0 : -1.0) * (top2 ? 1.0 : -1.0) *
-                                             ((lat == lat2 ? 1.0 : 0.0) - 1.0 / 3.0);
-                                    return v;
-                                };
-                                double w[3];
-                                for (int d2 = 0; d2 < 3; ++d2) {
-                                    if (!pc) {
-                                        w[d2] = entry(d2, ccomp);
-                                    } else {
-                                        w[d2] = 0.0;
-                                        for (int cc = 0; cc < 3; ++cc)
-                                            w[d2] += entry(d2, cc) * ((cc == ccomp ? 1.0 : 0.0) - nc[cc] * nc[ccomp]);
-                                    }
-                                }
-                                if (on_fs(ck + top2)) {
-                                    const double* nr = unit + 3 * ((((long long)q.d * (m + 1) + ci + cdi[wd][lat2]) *
-                                                                    (m + 1)) + cj + cdj[wd][lat2]);
-                                    const double dw = nr[0] * w[0] + nr[1] * w[1] + nr[2] * w[2];
-                                    for (int a2 = 0; a2 < 3; ++a2) w[a2] -= dw * nr[a2];
-                                }
-                                for (int d2 = 0; d2 < 3; ++d2) {
-                                    const int row = slot_dof[d2 * nslots + s2];
-                                    if (row < 0) continue;
-                                    Ad[(long long)col * nd + row] += w[d2];
-                                }
-                            }
-                        }
+    const int cs = dof_slot[col], rs = dof_slot[row];
+    const int cc = cs & 3, rc = rs & 3;
+    const int clat = (cs >> 2) / (n + 1), ck0 = (cs >> 2) % (n + 1);
+    const int rlat = (rs >> 2) / (n + 1), rk0 = (rs >> 2) % (n + 1);
+    const bool pc = on_fs(ck0), pr = on_fs(rk0), proj = pc || pr;
+    double M[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};   // [row component][column component]
+    if (rk0 - ck0 <= 1 && ck0 - rk0 <= 1) {
+        for (int r = 0; r < 6; ++r) {
+            const int cd = ring_tri[(size_t)clat * 6 + r];
+            if (cd < 0) break;
+            // which lateral vertex of the triangle the row's node is
+            const int v[3] = {clat, ring_nb[(size_t)clat * 6 + r], ring_nb[(size_t)clat * 6 + (r + 1) % 6]};
+            int s2 = -1;
+            for (int q = 0; q < 3; ++q)
+                if (slot_dof[rc * nslots + (long long)v[q] * (n + 1) + rk0] == row) s2 = q;
+            if (s2 < 0) continue;
+            const int cell = cd >> 3, wd = (cd >> 2) & 1, lat = cd & 3, lat2 = (lat + s2) % 3;
+            const double* g = geo + (size_t)cell * GEO_PER_COL + wd * GEO_PER_TRI;
+            for (int ck = ck0 - 1; ck <= ck0; ++ck) {
+                const int top = ck0 - ck, top2 = rk0 - ck;
+                if (ck < 0 || ck >= n || top2 < 0 || top2 > 1) continue;
+                const double rm = r_in + (ck + 0.5) * dr;
+                const double e = (double)eta[((size_t)cell * n + ck) * 2 + wd];
+                // quadrature points: q_c (weight 1), or the two radial points
+                for (int qq = 0; qq < (twopt ? 2 : 1); ++qq) {
+                    const double zq = twopt ? (qq == 0 ? -TWOPT_ZETA : TWOPT_ZETA) : 0.0;
+                    const double rq = twopt ? rm + zq * (0.5 * dr) : rm;
+                    const double V = (twopt ? 0.5 : 1.0) * rq * rq * g[9];
+                    double gj[3], gl[3];
+                    if (twopt) {
+                        basis_grad_at(g, 0.5 / rq, zq, lat, top, gj);
+                        basis_grad_at(g, 0.5 / rq, zq, lat2, top2, gl);
+                    } else {
+                        basis_grad(g, 0.5 / rm, lat, top, gj);
+                        basis_grad(g, 0.5 / rm, lat2, top2, gl);
                     }
+                    const double gg = gj[0] * gl[0] + gj[1] * gl[1] + gj[2] * gl[2];
+                    const double eps = hg_alpha != 0.0 ? hg_eps(g, 0.5 / rm, V, e, hg_alpha) : 0.0;
+                    // (A_e)_{(l,a),(j,b)} = V eta [delta_ab g_j.g_l + (g_j)_a (g_l)_b - 2/3 (g_j)_b (g_l)_a]
+                    // hourglass term: eps delta_ab zeta_j zeta_l (delta_{lat_j, lat_l} - 1/3)
+                    for (int a = 0; a < 3; ++a)
+                        for (int b = 0; b < 3; ++b) {
+                            if (!proj && (a != rc || b != cc)) continue;
+                            double w = V * e * ((a == b ? gg : 0.0) + gj[a] * gl[b] - (2.0 / 3.0) * gj[b] * gl[a]);
+                            if (a == b)
+                                w += eps * (top ? 1.0 : -1.0) * (top2 ? 1.0 : -1.0) *
+                                     ((lat == lat2 ? 1.0 : 0.0) - 1.0 / 3.0);
+                            M[a][b] += w;
+                        }
                 }
             }
         }
     }
-    // the normal row of a free-slip node: + N e_c = rhat rhat_c, once per DoF
-    {
-        const int sc = copy_slot[copy_ptr[col]];
-        const long long slot = sc >> 2;
-        const int ccomp = sc & 3;
-        const NodeIdx q = decode_node(slot, m, n);
-        if (on_fs(q.k)) {
-            const double* nc = unit + 3 * ((((long long)q.d * (m + 1) + q.i) * (m + 1)) + q.j);
-            for (int a2 = 0; a2 < 3; ++a2) {
-                const int row = slot_dof[a2 * nslots + slot];
-                if (row >= 0) Ad[(long long)col * nd + row] += nc[a2] * nc[ccomp];
-            }
+    double v = 0.0;
+    if (!proj) {
+        for (int a = 0; a < 3; ++a)
+            for (int b = 0; b < 3; ++b)
+                if (a == rc && b == cc) v = M[a][b];
+    } else {
+        const double* nc = unit + 3 * (size_t)clat;
+        const double* nr = unit + 3 * (size_t)rlat;
+        for (int a = 0; a < 3; ++a) {
+            double w = 0.0;
+            for (int b = 0; b < 3; ++b) w += M[a][b] * ((b == cc ? 1.0 : 0.0) - (pc ? nc[b] * nc[cc] : 0.0));
+            v += ((a == rc ? 1.0 : 0.0) - (pr ? nr[a] * nr[rc] : 0.0)) * w;
         }
+        // the normal rows of a free-slip node: + N
+        if (pc && clat == rlat && ck0 == rk0) v += nc[rc] * nc[cc];
     }
+    Ad[(size_t)col * nd + row] = v;
 }
 
 }  // namespace
@@ -1817,12 +1825,12 @@ void scal_scatter(const tng_ctx* ctx, const double* staging, int k, double* dst)
 }
 
 template <typename T>
-void coarse_assemble(const tng_ctx* ctx, const CoarseDense& cd, const Level& L, const T* eta, double hg_alpha,
+void coarse_assemble(const tng_ctx* ctx, CoarseDense& cd, const Level& L, const T* eta, double hg_alpha,
                      bool twopt, unsigned fs) {
     require_unbatched("coarse_assemble");
-    coarse_assemble_kernel<T><<<nblk(cd.ndof, 64), 64, 0, ctx->stream>>>(
-        cd.ndof, cd.copy_ptr.p, cd.copy_slot.p, cd.slot_dof.p, cd.nslots, eta, L.geo64.p, L.m, L.n, L.r_in,
-        L.dr(), hg_alpha, twopt ? 1 : 0, (int)fs, L.unit64.p, cd.Ainv.p);
+    coarse_assemble_kernel<T><<<dim3(nblk(cd.ndof, 64), cd.ndof), 64, 0, ctx->stream>>>(
+        cd.ndof, cd.dof_slot.p, cd.slot_dof.p, cd.nslots, L.ring_tri.p, L.ring_nb.p, eta, L.geo64.p, L.m, L.n, L.r_in,
+        L.dr(), hg_alpha, twopt ? 1 : 0, (int)fs, L.unit64.p, cd.matrix());
     TNG_HIP(hipGetLastError());
 }
 
@@ -1843,29 +1851,13 @@ void vec_fill(const tng_ctx* ctx, long long n, T v, T* a) {
     TNG_HIP(hipGetLastError());
 }
 
-template <typename T>
-void coarse_unit(const tng_ctx* ctx, const CoarseDense& cd, int col, T* const x[3]) {
-    require_unbatched("coarse_unit");
-    unit_vector_kernel<T><<<nblk(3 * cd.nslots, 256), 256, 0, ctx->stream>>>(cd.nslots, cd.slot_dof.p, col, x[0],
-                                                                             x[1], x[2]);
-    TNG_HIP(hipGetLastError());
-}
-
-template <typename T>
-void coarse_gather(const tng_ctx* ctx, const CoarseDense& cd, int col, const T* const y[3], double* Ad) {
-    require_unbatched("coarse_gather");
-    coarse_gather_col_kernel<T><<<nblk(cd.ndof, 256), 256, 0, ctx->stream>>>(cd.ndof, cd.dof_slot.p, y[0], y[1],
-                                                                              y[2], col, Ad);
-    TNG_HIP(hipGetLastError());
-}
-
 void coarse_rotation_shift(const tng_ctx* ctx, CoarseDense& cd, const Level& L) {
     require_unbatched("coarse_rotation_shift");
     if (cd.rotq.n != (size_t)(3 * cd.ndof + 1)) cd.rotq.alloc(3 * cd.ndof + 1);
     coarse_rotation_basis_kernel<<<1, 1, 0, ctx->stream>>>(cd.ndof, cd.dof_slot.p, L.m, L.n, L.r_in, L.dr(),
-                                                         L.unit64.p, cd.Ainv.p, cd.rotq.p);
+                                                         L.unit64.p, cd.matrix(), cd.rotq.p);
     TNG_HIP(hipGetLastError());
-    coarse_rotation_shift_kernel<<<nblk(cd.ndof, 64), 64, 0, ctx->stream>>>(cd.ndof, cd.rotq.p, cd.Ainv.p);
+    coarse_rotation_shift_kernel<<<nblk(cd.ndof, 64), 64, 0, ctx->stream>>>(cd.ndof, cd.rotq.p, cd.matrix());
     TNG_HIP(hipGetLastError());
 }
 
@@ -1880,8 +1872,14 @@ void vec_rotation(const tng_ctx* ctx, const Level& L, int a, T* const out[3]) {
 
 void coarse_invert(const tng_ctx* ctx, CoarseDense& cd) {
     require_unbatched("coarse_invert");
-    gauss_jordan_kernel<<<1, 1024, 0, ctx->stream>>>(cd.ndof, cd.Ainv.p);
-    TNG_HIP(hipGetLastError());
+    const int nb = cd.inv_steps();
+    double* a = cd.matrix();
+    for (int pb = 0; pb < nb; ++pb) {
+        double* o = a == cd.Ainv.p ? cd.Awork.p : cd.Ainv.p;
+        invert_step_kernel<<<dim3(nb, nb), 256, 0, ctx->stream>>>(cd.ndof, pb, a, o);
+        TNG_HIP(hipGetLastError());
+        a = o;
+    }
 }
 
 template <typename T>
@@ -1923,8 +1921,6 @@ void vec_schur(const tng_ctx* ctx, long long n, const T* r, const T* mdiag, T* z
     template void vec_axpby<T>(const tng_ctx*, long long, double, const T*, double, T*);                  \
     template void vec_mdot<T>(const tng_ctx*, DotScratch&, long long, int, long long, const uint8_t*,     \
                               const T*, const T* const*, int, double*, bool);                              \
-    template void coarse_unit<T>(const tng_ctx*, const CoarseDense&, int, T* const[3]);                   \
-    template void coarse_gather<T>(const tng_ctx*, const CoarseDense&, int, const T* const[3], double*);  \
     template void coarse_solve<T>(const tng_ctx*, const CoarseDense&, const T* const[3], T* const[3]);    \
     template void vec_shift<T>(const tng_ctx*, long long, const double*, T*);                             \
     template void vec_schur<T>(const tng_ctx*, long long, const T*, const T*, T*);                       \
@@ -1939,7 +1935,7 @@ void vec_schur(const tng_ctx* ctx, long long n, const T* r, const T* mdiag, T* z
     template void vec_scale_rsqrt<T>(const tng_ctx*, long long, const double*, const T*, T*);             \
     template void vec_tab_copy<T>(const tng_ctx*, long long, const T*, const T* const*, T*, T* const*, int, \
                                   const double*);                                                          \
-    template void coarse_assemble<T>(const tng_ctx*, const CoarseDense&, const Level&, const T*, double, bool,  \
+    template void coarse_assemble<T>(const tng_ctx*, CoarseDense&, const Level&, const T*, double, bool,  \
                                      unsigned);
 TNG_INST(double)
 TNG_INST(float)

@@ -308,6 +308,10 @@ void chebyshev_fs(tng_solver* s, int l, const T* b, T* x, bool x_zero, int steps
 
 template <typename T>
 void chebyshev(tng_solver* s, int l, const T* b, T* x, bool x_zero, int steps) {
+    if (x_zero && steps == 0) {   // no pre-smoothing: the cycle still starts from zero
+        vec_fill<T>(s->ctx, 3 * hier<T>(s)[l].ns, T(0), x);
+        return;
+    }
     if (fs_flag(s)) {
         chebyshev_fs<T>(s, l, b, x, x_zero, steps);
         return;
@@ -559,31 +563,21 @@ void build_coarse_maps(tng_solver* s) {
         throw Error(TNG_E_INVAL, "coarsest level has " + std::to_string(nd) + " interior DoFs (max " +
                                      std::to_string(MAX_COARSE_DOF) + "); build more levels");
     std::vector<int> slot_dof((size_t)3 * nsl, -1);
-    std::vector<std::vector<int>> copies(nd);
     for (long long q = 0; q < nl; ++q)
         for (int k = k0; k <= k1; ++k)
             for (int c = 0; c < 3; ++c) {
                 const int dof = dof_of_uid_k[((size_t)C.uid[q] * (n + 1) + k) * 3 + c];
                 const long long slot = q * (n + 1) + k;
                 slot_dof[(size_t)c * nsl + slot] = dof;
-                copies[dof].push_back((int)((slot << 2) | c));
             }
-    std::vector<int> cptr(1, 0), cslot;
-    for (auto& v : copies) {
-        cslot.insert(cslot.end(), v.begin(), v.end());
-        cptr.push_back((int)cslot.size());
-    }
     s->cd.ndof = nd;
     s->cd.nslots = nsl;
     s->cd.dof_slot.alloc(nd);
     TNG_HIP(hipMemcpy(s->cd.dof_slot.p, dof_slot.data(), nd * sizeof(int), hipMemcpyHostToDevice));
     s->cd.slot_dof.alloc(slot_dof.size());
     TNG_HIP(hipMemcpy(s->cd.slot_dof.p, slot_dof.data(), slot_dof.size() * sizeof(int), hipMemcpyHostToDevice));
-    s->cd.copy_ptr.alloc(cptr.size());
-    TNG_HIP(hipMemcpy(s->cd.copy_ptr.p, cptr.data(), cptr.size() * sizeof(int), hipMemcpyHostToDevice));
-    s->cd.copy_slot.alloc(cslot.size());
-    TNG_HIP(hipMemcpy(s->cd.copy_slot.p, cslot.data(), cslot.size() * sizeof(int), hipMemcpyHostToDevice));
     s->cd.Ainv.alloc((size_t)nd * nd);
+    s->cd.Awork.alloc((size_t)nd * nd);
 }
 
 template <typename T>

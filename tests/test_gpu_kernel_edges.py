@@ -4,11 +4,13 @@ fused kernels of the solver, at the edges of their decompositions: the smallest 
 sizes, and the largest radial counts of the streamed kernels."""
 import numpy as np
 import pytest
+import scipy.sparse as sp
+import scipy.sparse.linalg as spla
 
 import synthetic
 from oracle.mesh import ShellMesh
-from oracle.solver_ref import lumped_pressure_mass
-from oracle.stokes import StokesOracle, buoyancy_rhs
+from oracle.solver_ref import lumped_pressure_mass, velocity_prolongation
+from oracle.stokes import StokesOracle, buoyancy_rhs, element_matrices
 from tests._support import LayoutMap
 
 pytestmark = pytest.mark.gpu
@@ -75,3 +77,39 @@ def test_diagonal_pressure_mass_buoyancy(tng, ctx, dtype, tol, mt, nr):
     assert (np.abs(got_d - want_d) <= tol * np.abs(want_d)).all()
     assert (np.abs(got_m - want_m) <= tol * np.abs(want_m)).all()
     assert np.abs(got_f - want_f).max() <= 10 * tol * np.abs(want_f).max()
+
+
+# unknowns of the coarsest level: 126 (a part of a pivot block left over), 252 and 486, and
+# 1008 (the largest that the refinement leaves below the limit of 1024)
+@pytest.mark.parametrize("mt,nr", [(4, 4), (4, 6), (8, 4), (4, 18)])
+def test_coarse_correction(tng, ctx, mt, nr):
+    """A V-cycle without smoothing is P A_c^-1 P^T: assembly, blocked inverse and solve of the
+    coarsest level against the oracle's sparse solve, to 1e-10 (the matrix's condition number,
+    below 1e4 on these shells, times 50 roundings)."""
+    import torch
+    mesh, om, omp, lm, lmp, eta, orc = shell(tng, ctx, mt, nr)
+    eta_t = torch.tensor(eta[lm.wedge_index()], device="cuda")
+    eta_c = torch.empty(mesh.wedge_shape(1), dtype=torch.float64, device="cuda")
+    tng.eta_coarsen(ctx, mesh, 0, eta_t, eta_c)
+    ec = np.empty(omp.n_wedges)
+    ec[lmp.wedge_index().ravel()] = eta_c.cpu().numpy().ravel()
+    s = tng.StokesSolver(ctx, mesh, mixed=0, levels=2, pre=0, post=0)
+    s.setup(eta_t)
+    b = np.random.default_rng(6).standard_normal((om.n_nodes, 3))
+    b[om.boundary_nodes()] = 0.0
+    bt = torch.tensor(lm.to_lib(b), device="cuda").contiguous()
+    x = torch.full_like(bt, float("nan"))
+    s.vcycle(bt, x)
+    torch.cuda.synchronize()
+    P = velocity_prolongation(orc)
+    wn = omp.wedge_nodes()
+    dof = (wn[:, :, None] * 3 + np.arange(3)).reshape(len(wn), 18)
+    A = sp.csr_matrix((element_matrices(omp.node_xyz()[wn], ec).ravel(),
+                       (np.repeat(dof, 18, axis=1).ravel(), np.tile(dof, (1, 18)).ravel())))
+    inner = np.setdiff1d(np.arange(3 * omp.n_nodes),
+                         (3 * np.flatnonzero(omp.boundary_nodes())[:, None] + np.arange(3)).ravel())
+    c = np.zeros(3 * omp.n_nodes)
+    c[inner] = spla.spsolve(A[inner][:, inner].tocsc(), (P.T @ b.ravel())[inner])
+    want = (P @ c).reshape(-1, 3)
+    got = lm.from_lib(x.cpu().numpy(), check_dups=1e-13)
+    assert np.linalg.norm(got - want) <= 1e-10 * np.linalg.norm(want)
