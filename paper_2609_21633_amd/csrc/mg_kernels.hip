@@ -780,7 +780,7 @@ __device__ __forceinline__ gptr<T> as_global(const T* p) {
     return (gptr<T>)p;
 }
 
-// Block sums of acc[q], q < nq, to part[blockIdx.x][q] (fixed order).
+// Block sums of acc[q], q < nq, to part[q][blockIdx.x] (fixed order).
 template <int NQ>
 __device__ __forceinline__ void block_partials(const double (&acc)[NQ], int nq, double* __restrict__ part) {
     __shared__ double sh[DOT_BS / 64][NQ];
@@ -796,7 +796,7 @@ __device__ __forceinline__ void block_partials(const double (&acc)[NQ], int nq, 
     if (threadIdx.x < nq) {
         double v = 0.0;
         for (int w = 0; w < DOT_BS / 64; ++w) v += sh[w][threadIdx.x];
-        part[(long long)blockIdx.x * MAX_MDOT + threadIdx.x] = v;
+        part[(long long)threadIdx.x * DOT_BLOCKS + blockIdx.x] = v;
     }
 }
 
@@ -899,28 +899,31 @@ __global__ void fillv_kernel(unsigned n, T v, T* a, SlotBatch sb) {
     for (unsigned t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) a[t] = v;
 }
 
-// out[q] = sum of the block partials of vector q: wave w takes q = w, w + 4,
-// ..., every lane a fixed strided share of the blocks, then a fixed shuffle
-// tree; the order depends only on nblocks.
+// out[q] = sum of the block partials of vector q = blockIdx.x: every thread a fixed strided
+// share of the contiguous partials, then a fixed shuffle tree and the waves in order; the
+// order depends only on nblocks.  One workgroup per vector and coalesced reads (a single
+// workgroup gathering strided partials took 12.8 us for 4096 blocks).
 __global__ void __launch_bounds__(256) mdot_final_kernel(int nblocks, int nq, const double* __restrict__ part,
                                                          double* out, int accumulate, SlotBatch sb) {
     const long long so = slot_off(sb);
     part = at_slot(part, so);
     out = at_slot(out, so);
-    nq = slot_count(sb, nq);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int q = wv; q < nq; q += 4) {
-        // eight independent partial sums per lane keep eight loads in flight (the loads
-        // are a strided gather, latency-bound one by one); combined in a fixed order
-        double v8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        int b = lane;
-        for (; b + 7 * 64 < nblocks; b += 8 * 64)
+    const int q = blockIdx.x;
+    if (q >= slot_count(sb, nq)) return;
+    part += (size_t)q * DOT_BLOCKS;
+    double v = 0.0;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v8[u] += part[(long long)(b + u * 64) * MAX_MDOT + q];
-        for (; b < nblocks; b += 64) v8[0] += part[(long long)b * MAX_MDOT + q];
-        double v = ((v8[0] + v8[1]) + (v8[2] + v8[3])) + ((v8[4] + v8[5]) + (v8[6] + v8[7]));
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-        if (lane == 0) out[q] = accumulate ? out[q] + v : v;
+    for (int u = 0; u < DOT_BLOCKS / 256; ++u) {
+        const int b = threadIdx.x + 256 * u;
+        v += b < nblocks ? part[b] : 0.0;
+    }
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    __shared__ double sh[4];
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        v = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+        out[q] = accumulate ? out[q] + v : v;
     }
 }
 
@@ -1684,7 +1687,7 @@ void vec_mdot(const tng_ctx* ctx, DotScratch& ds, long long n, int n1, long long
                     (mdot_partial_kernel<T, NQ><<<dim3(nb, 1, sb.nb), DOT_BS, 0, ctx->stream>>>(
                         (unsigned)n, dn1, (unsigned)nlat, owner, x, vs_dev, nq, ds.part.p, sb)));
     TNG_HIP(hipGetLastError());
-    mdot_final_kernel<<<dim3(1, 1, sb.nb), 256, 0, ctx->stream>>>(nb, nq, ds.part.p, out_dev, accumulate ? 1 : 0, sb);
+    mdot_final_kernel<<<dim3(count_class(sb, nq), 1, sb.nb), 256, 0, ctx->stream>>>(nb, nq, ds.part.p, out_dev, accumulate ? 1 : 0, sb);
     TNG_HIP(hipGetLastError());
 }
 
@@ -1719,7 +1722,7 @@ void vec_smdot(const tng_ctx* ctx, DotScratch& ds, const Level& Lu, const Level&
                                 (unsigned)Lu.node_slots(), du, (unsigned)Lu.lat_slots(), Lu.owner.p,
                                 (unsigned)Lp.node_slots(), dp, Lp.owner.p, x, vs_dev, nq, ds.part.p, sb)));
         TNG_HIP(hipGetLastError());
-        mdot_final_kernel<<<dim3(1, 1, sb.nb), 256, 0, ctx->stream>>>(nb, nq, ds.part.p, out_dev,
+        mdot_final_kernel<<<dim3(count_class(sb, nq), 1, sb.nb), 256, 0, ctx->stream>>>(nb, nq, ds.part.p, out_dev,
                                                                       accumulate ? 1 : 0, sb);
         TNG_HIP(hipGetLastError());
         return;
@@ -1730,7 +1733,7 @@ void vec_smdot(const tng_ctx* ctx, DotScratch& ds, const Level& Lu, const Level&
                         (unsigned)Lu.node_slots(), du, (unsigned)Lu.lat_slots(), Lu.owner.p,
                         (unsigned)Lp.node_slots(), dp, Lp.owner.p, x, vs_dev, nq, ds.part.p, sb)));
     TNG_HIP(hipGetLastError());
-    mdot_final_kernel<<<dim3(1, 1, sb.nb), 256, 0, ctx->stream>>>(nb, nq, ds.part.p, out_dev, accumulate ? 1 : 0, sb);
+    mdot_final_kernel<<<dim3(count_class(sb, nq), 1, sb.nb), 256, 0, ctx->stream>>>(nb, nq, ds.part.p, out_dev, accumulate ? 1 : 0, sb);
     TNG_HIP(hipGetLastError());
 }
 
@@ -1762,7 +1765,7 @@ void vec_maxpy_smdot(const tng_ctx* ctx, DotScratch& ds, const Level& Lu, const 
         // the norm has one value for every slot: the per-slot counts do not apply to it
         SlotBatch sf = sb;
         if (norm) sf.has_cnt = 0;
-        mdot_final_kernel<<<dim3(1, 1, sf.nb), 256, 0, ctx->stream>>>(nb, norm ? 1 : nq, ds.part.p, out_dev, 0, sf);
+        mdot_final_kernel<<<dim3(norm ? 1 : count_class(sf, nq), 1, sf.nb), 256, 0, ctx->stream>>>(nb, norm ? 1 : nq, ds.part.p, out_dev, 0, sf);
         TNG_HIP(hipGetLastError());
         return;
     }
@@ -1782,7 +1785,7 @@ void vec_maxpy_smdot(const tng_ctx* ctx, DotScratch& ds, const Level& Lu, const 
     // the norm has one value for every slot: the per-slot counts do not apply to it
     SlotBatch sf = sb;
     if (norm) sf.has_cnt = 0;
-    mdot_final_kernel<<<dim3(1, 1, sf.nb), 256, 0, ctx->stream>>>(nb, norm ? 1 : nq, ds.part.p, out_dev, 0, sf);
+    mdot_final_kernel<<<dim3(norm ? 1 : count_class(sf, nq), 1, sf.nb), 256, 0, ctx->stream>>>(nb, norm ? 1 : nq, ds.part.p, out_dev, 0, sf);
     TNG_HIP(hipGetLastError());
 }
 
