@@ -17,7 +17,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtng.so")
 SOURCES = ["capi.cpp", "mesh.cpp", "stokes_apply.hip", "interface.hip", "fields.hip", "mg_kernels.hip", "solver.cpp",
            "energy.hip", "energy.cpp", "server.cpp", "noalloc.hip", "bandwidth.hip", "mmoc.hip",
-           "energy_stream.hip"]
+           "energy_stream.hip", "ring_smooth.hip"]
 ARCH = "gfx950"
 
 

@@ -51,6 +51,9 @@ __device__ __forceinline__ unsigned xcd_block() {
 }
 
 // Lane l receives lane l - 1's value, lane 0 zero (DPP wavefront shift).
+__device__ __forceinline__ float lane_below(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
 __device__ __forceinline__ double lane_below(double v) {
     const long long b = __double_as_longlong(v);
     const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x138, 0xf, 0xf, true);

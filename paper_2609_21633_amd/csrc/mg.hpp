@@ -83,6 +83,20 @@ void vec_cheb_post_update(const tng_ctx* ctx, const Level& L, bool ns_in, bool n
 template <typename T>
 void vec_resid_post(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* b, const T* x, const T* y,
                     T* r);
+// The same three uses of A_D x as one launch each (ring_smooth.hip), without hourglass
+// control and on levels where ring_apply_fits: a Chebyshev step, a residual, and a step of
+// the power iteration z = D^-1 A_D x.
+template <typename T>
+bool ring_apply_fits(const Level& L);
+template <typename T>
+void ring_cheb_step(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* eta, const double* ab_dev,
+                    int k, bool prev_zero, const T* b, const T* invd, const T* xk, T* xo);
+template <typename T>
+void ring_resid(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* eta, const T* b, const T* x,
+                T* r);
+template <typename T>
+void ring_power(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* eta, const T* invd, const T* x,
+                T* z);
 template <typename T>
 void vec_invert(const tng_ctx* ctx, long long n, T* a);
 template <typename TO, typename TI>

@@ -1,0 +1,234 @@
+// The viscous operator on small multigrid levels, gathered per node and fused with what
+// the smoother does with it (Sec. 7): one launch per Chebyshev step, residual or power
+// iteration step instead of seam zeroing, operator apply and update.
+//
+// The streaming apply (stokes_apply.hip) walks the cell rows of a band one after another,
+// about ten microseconds on any small level however few cells it has.  Here a workgroup
+// takes 63 consecutive node slots and gives each of their six triangles a wave: a lane
+// forms the stress of the wedge above its node in its triangle, and the parts of the two
+// nodes of that wedge in its column: its own (bottom) and the next lane's (top, handed on
+// by a DPP shift; lane 0 only serves lane 1).  The six triangles' parts are added in LDS
+// in ring order, over all diamonds, so that every copy of a node gets the same bits and no
+// interface pass is needed.  A wedge is evaluated for each of its three columns, against
+// once in the streaming apply, so this form is for levels whose launches are bound by
+// latency (ring_apply_fits).
+//
+// With E1 = sum over the wedge's two layers of u_1 - u_0, E2 of u_2 - u_0 (node 0 the
+// lane's own), C the difference between its layers of u_0 + u_1 + u_2, a_l the lateral
+// basis gradients and g3 the radial row (wedge.hpp, rows without their 1/(2 r_m)),
+//   2 r_m grad u = L = E1 a_1 + E2 a_2 + 2 r_m C g3,  2 r_m grad phi_0 = a_0 +- 2 r_m g3,
+// and V / (2 r_m)^2 = g9 / 4: the wedge's part of row 0 is
+//   eta g9/4 (L + L^T - 2/3 tr L) (a_0 +- 2 r_m g3), with no division (+ at its top node).
+#include "batch_dev.hpp"
+#include "mg.hpp"
+#include "tng_internal.hpp"
+
+namespace tng {
+namespace {
+
+enum { RING_CHEB, RING_RESID, RING_POWER };
+
+template <typename T>
+struct RingArgs {
+    const int* __restrict__ ring_tri;
+    const int* __restrict__ ring_nb;
+    const T* __restrict__ geo;
+    const T* __restrict__ eta;
+    const T* __restrict__ x;      // velocity the operator is applied to
+    const T* __restrict__ b;      // right-hand side (step, residual)
+    const T* __restrict__ invd;   // inverse diagonal (step, power iteration)
+    T* out;                       // step: x_k-1 in, x_k+1 out; residual; power: D^-1 A_D x
+    const double* __restrict__ ab;
+    int k;                        // step of the recurrence
+    int prev_zero;
+    unsigned ns;
+    int n;
+    MagicDiv dn1;
+    T r_in, dr;
+    int ns_in, ns_out;
+};
+
+template <typename T, int MODE>
+__global__ void __launch_bounds__(384) ring_apply_kernel(RingArgs<T> a, SlotBatch sb) {
+    __shared__ T part[6][3][64];
+    const long long so = slot_off(sb);
+    const T* eta = at_slot(a.eta, so);
+    const T* x = at_slot(a.x, so);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int ti = (int)(xcd_block() * 63u) + lane - 1;      // node slot; lane 0: the one below the first
+    const bool mine = lane > 0 && ti < (int)a.ns;
+    const unsigned t = (unsigned)min(max(ti, 0), (int)a.ns - 1);
+    const int n = a.n, n1 = n + 1;
+    const unsigned lat = mdiv(t, a.dn1);
+    const int k = (int)(t - lat * (unsigned)n1);
+    const bool off0 = a.ns_in && k == 0, offn = a.ns_out && k == n;
+    // what the closing threads (wave w < 3: component w) need, on its way early
+    T bv = T(0), iv = T(0), xv = T(0), pv = T(0), alpha = T(0), beta = T(0);
+    const size_t e = (size_t)w * a.ns + t;
+    if (w < 3) {
+        if constexpr (MODE != RING_POWER) bv = at_slot(a.b, so)[e];
+        if constexpr (MODE != RING_RESID) iv = at_slot(a.invd, so)[e];
+        xv = x[e];
+        if constexpr (MODE == RING_CHEB) {
+            const double* ab = at_slot(a.ab, so);
+            alpha = T(ab[2 * a.k]);
+            beta = T(ab[2 * a.k + 1]);
+            if (alpha != T(0) && !a.prev_zero) pv = at_slot(a.out, so)[e];
+        }
+    }
+    T bot[3] = {T(0), T(0), T(0)}, top[3] = {T(0), T(0), T(0)};
+    const int code = a.ring_tri[lat * 6 + w];
+    if (code >= 0 && k < n && ti >= 0) {
+        const int cell = code >> 3, wd = (code >> 2) & 1, l = code & 3;
+        const unsigned v[3] = {lat, (unsigned)a.ring_nb[lat * 6 + w], (unsigned)a.ring_nb[lat * 6 + (w < 5 ? w + 1 : 0)]};
+        const T* g = a.geo + (size_t)cell * GEO_PER_COL + wd * GEO_PER_TRI;
+        T u[2][3][3];   // [layer k, k + 1][vertex][component]
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const T* xc = x + ((size_t)c * a.ns + v[s] * (unsigned)n1 + k);
+                u[0][s][c] = xc[0];
+                u[1][s][c] = xc[1];
+            }
+        const T ev = T(0.25) * g[9] * eta[((size_t)cell * n + k) * 2 + wd];
+        // velocities on no-slip layers count as zero
+        const bool z0 = off0, z1 = a.ns_out && k + 1 == n;
+        T a1[3], a2[3], g3[3], L[3][3];
+        const T r2 = T(2) * (a.r_in + (T(k) + T(0.5)) * a.dr);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const T g0 = g[c], g1 = g[3 + c], gm = -(g0 + g1);
+            a1[c] = l == 0 ? g0 : (l == 1 ? g1 : gm);
+            a2[c] = l == 0 ? g1 : (l == 1 ? gm : g0);
+            g3[c] = r2 * g[6 + c];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const T b0 = z0 ? T(0) : u[0][0][c], b1 = z0 ? T(0) : u[0][1][c], b2 = z0 ? T(0) : u[0][2][c];
+            const T t0 = z1 ? T(0) : u[1][0][c], t1 = z1 ? T(0) : u[1][1][c], t2 = z1 ? T(0) : u[1][2][c];
+            const T E1 = (b1 - b0) + (t1 - t0), E2 = (b2 - b0) + (t2 - t0);
+            const T C = (t0 + t1 + t2) - (b0 + b1 + b2);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) L[c][d] = E1 * a1[d] + E2 * a2[d] + C * g3[d];
+        }
+        const T tr = T(2.0 / 3.0) * (L[0][0] + L[1][1] + L[2][2]);
+        T S[3][3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            S[c][c] = ev * (L[c][c] + L[c][c] - tr);
+            const int d = (c + 1) % 3;
+            S[c][d] = S[d][c] = ev * (L[c][d] + L[d][c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const T P = -(S[c][0] * (a1[0] + a2[0]) + S[c][1] * (a1[1] + a2[1]) + S[c][2] * (a1[2] + a2[2]));
+            const T Q = S[c][0] * g3[0] + S[c][1] * g3[1] + S[c][2] * g3[2];
+            bot[c] = P - Q;
+            top[c] = P + Q;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) part[w][c][lane] = bot[c] + lane_below(top[c]);
+    __syncthreads();
+    if (w >= 3 || !mine) return;
+    T yv = part[0][w][lane];
+#pragma unroll
+    for (int r = 1; r < 6; ++r) yv += part[r][w][lane];
+    const bool bnd = off0 || offn;
+    if (bnd) yv = xv;
+    T* out = at_slot(a.out, so);
+    if constexpr (MODE == RING_RESID) {
+        out[e] = bv - yv;
+    } else if constexpr (MODE == RING_POWER) {
+        out[e] = iv * yv;
+    } else {
+        // as cheb_post_update_kernel
+        const T r = beta * iv * (bv - yv);
+        const bool use_prev = alpha != T(0) && !a.prev_zero;
+        out[e] = use_prev ? xv + (alpha * (xv - pv) + r) : (alpha == T(0) ? xv + r : xv + (alpha * xv + r));
+    }
+}
+
+template <typename T>
+RingArgs<T> ring_args(const Level& L, bool ns_in, bool ns_out, const T* eta, const T* x) {
+    RingArgs<T> a{};
+    constexpr bool is64 = sizeof(T) == 8;
+    a.ring_tri = L.ring_tri.p;
+    a.ring_nb = L.ring_nb.p;
+    a.geo = is64 ? reinterpret_cast<const T*>(L.geo64.p) : reinterpret_cast<const T*>(L.geo32.p);
+    a.eta = eta;
+    a.x = x;
+    a.ns = (unsigned)L.node_slots();
+    a.n = L.n;
+    a.dn1 = magic_div((unsigned)(L.n + 1));
+    a.r_in = T(L.r_in);
+    a.dr = T(L.dr());
+    a.ns_in = ns_in ? 1 : 0;
+    a.ns_out = ns_out ? 1 : 0;
+    return a;
+}
+
+template <typename T, int MODE>
+void ring_launch(const tng_ctx* ctx, const Level& L, const RingArgs<T>& a) {
+    const SlotBatch sb = launch_batch();
+    const unsigned nb = (unsigned)((L.node_slots() + 62) / 63);
+    ring_apply_kernel<T, MODE><<<dim3(nb, 1, sb.nb), 384, 0, ctx->stream>>>(a, sb);
+    TNG_HIP(hipGetLastError());
+}
+
+}  // namespace
+
+// Where one gathered launch beats seam zeroing, streaming apply and update.  V-cycle times
+// with the level's seven steps and residual one way or the other: (16,16) FP64 463 -> 231
+// us, FP32 391 -> 185 us for the levels up to 49,130 slots; (32,32), 359,370 slots, FP32
+// 452 -> 356 us but FP64 540 -> 583 us; (64,64), 2.7 M slots, FP32 1006 -> 1355 us.  The
+// gathered form grows with the slots, the streaming one hardly below a million, so the
+// lines lie between the measured sizes.
+template <typename T>
+bool ring_apply_fits(const Level& L) {
+    return L.node_slots() <= (sizeof(T) == 8 ? 200000 : 800000);
+}
+
+template <typename T>
+void ring_cheb_step(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* eta, const double* ab_dev,
+                    int k, bool prev_zero, const T* b, const T* invd, const T* xk, T* xo) {
+    RingArgs<T> a = ring_args<T>(L, ns_in, ns_out, eta, xk);
+    a.b = b;
+    a.invd = invd;
+    a.out = xo;
+    a.ab = ab_dev;
+    a.k = k;
+    a.prev_zero = prev_zero ? 1 : 0;
+    ring_launch<T, RING_CHEB>(ctx, L, a);
+}
+
+template <typename T>
+void ring_resid(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* eta, const T* b, const T* x,
+                T* r) {
+    RingArgs<T> a = ring_args<T>(L, ns_in, ns_out, eta, x);
+    a.b = b;
+    a.out = r;
+    ring_launch<T, RING_RESID>(ctx, L, a);
+}
+
+template <typename T>
+void ring_power(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* eta, const T* invd, const T* x,
+                T* z) {
+    RingArgs<T> a = ring_args<T>(L, ns_in, ns_out, eta, x);
+    a.invd = invd;
+    a.out = z;
+    ring_launch<T, RING_POWER>(ctx, L, a);
+}
+
+#define TNG_RINST(T)                                                                                             \
+    template bool ring_apply_fits<T>(const Level&);                                                              \
+    template void ring_cheb_step<T>(const tng_ctx*, const Level&, bool, bool, const T*, const double*, int, bool,    \
+                                    const T*, const T*, const T*, T*);                                            \
+    template void ring_resid<T>(const tng_ctx*, const Level&, bool, bool, const T*, const T*, const T*, T*);          \
+    template void ring_power<T>(const tng_ctx*, const Level&, bool, bool, const T*, const T*, const T*, T*);
+TNG_RINST(double)
+TNG_RINST(float)
+#undef TNG_RINST
+
+}  // namespace tng

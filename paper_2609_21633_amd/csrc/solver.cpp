@@ -271,12 +271,17 @@ void chebyshev_steps(const tng_ctx* ctx, const Level& L, const T* eta, double hg
         void* yu[3] = {yout, yout + ns, yout + 2 * ns};
         launch_stokes_apply_raw(ctx, L, prec_of<T>(), aflags, hg_alpha, eta, u, yu);
     };
+    const bool ring = !twopt && hg_alpha == 0.0 && ring_apply_fits<T>(L);   // small levels: one launch per step
     for (int st = 0; st < steps; ++st) {
         for (int k = 0; k < deg; ++k) {
             const bool first = x_zero && st == 0 && k == 0;
             const bool prev_zero = x_zero && st == 0 && k == 1;   // x_k-1 is the zero start
             T* cur = (k & 1) ? d : x;
             T* out = (k & 1) ? x : d;
+            if (ring && !first) {
+                ring_cheb_step<T>(ctx, L, true, true, eta, ab_dev, k, prev_zero, b, invd, cur, out);
+                continue;
+            }
             if (!first) applyA(cur, y);
             vec_cheb_post_update<T>(ctx, L, true, true, ab_dev, k, first, prev_zero, b, y, invd, cur, out);
         }
@@ -340,6 +345,8 @@ void vcycle(tng_solver* s, int l, const T* b, T* x) {
         apply_A<T>(s, l, M.eta.p, x, M.y.p);
         vec_cast<T, T>(s->ctx, 3 * ns, b, M.r.p);
         vec_axpby<T>(s->ctx, 3 * ns, -1.0, M.y.p, 1.0, M.r.p);
+    } else if (!twopt_flag(s) && s->opts.hg_alpha == 0.0 && ring_apply_fits<T>(*M.L)) {
+        ring_resid<T>(s->ctx, *M.L, true, true, M.eta.p, b, x, M.r.p);
     } else {
         const Level& L = *M.L;
         const void* u[3] = {x, x + ns, x + 2 * ns};

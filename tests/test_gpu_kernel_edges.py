@@ -9,8 +9,8 @@ import scipy.sparse.linalg as spla
 
 import synthetic
 from oracle.mesh import ShellMesh
-from oracle.solver_ref import lumped_pressure_mass, velocity_prolongation
-from oracle.stokes import StokesOracle, buoyancy_rhs, element_matrices
+from oracle.solver_ref import chebyshev, lumped_pressure_mass, velocity_prolongation
+from oracle.stokes import StokesOracle, buoyancy_rhs, element_matrices, element_matrices_hg
 from tests._support import LayoutMap
 
 pytestmark = pytest.mark.gpu
@@ -113,3 +113,36 @@ def test_coarse_correction(tng, ctx, mt, nr):
     want = (P @ c).reshape(-1, 3)
     got = lm.from_lib(x.cpu().numpy(), check_dups=1e-13)
     assert np.linalg.norm(got - want) <= 1e-10 * np.linalg.norm(want)
+
+
+# gathered smoother: the smallest shell, 63-node blocks around the columns (62, 63 and 64
+# layers) and several blocks; with hourglass control (hg) the streaming apply and its update
+@pytest.mark.parametrize("dtype,tol", [("float64", 1e-12), ("float32", 1e-5)])
+@pytest.mark.parametrize("mt,nr,degree,hg", [(2, 2, 2, 0.0), (4, 61, 2, 0.0), (4, 62, 3, 0.0), (8, 63, 1, 0.0),
+                                             (16, 12, 2, 0.0), (16, 12, 2, 0.1), (8, 62, 3, 0.1)])
+def test_smoother(tng, ctx, dtype, tol, mt, nr, degree, hg):
+    """Two Chebyshev steps against the textbook iteration on the assembled operator, also with
+    non-zero boundary velocities (their columns are dropped, their rows are identity)."""
+    import torch
+    dt = getattr(torch, dtype)
+    mesh = tng.Mesh(ctx, mt, nr, levels=1)
+    om = ShellMesh(mt, nr)
+    lm = LayoutMap(*mesh.coords(0), om)
+    eta = 10.0 ** np.random.default_rng(5).uniform(-1.0, 1.0, om.n_wedges)
+    wn = om.wedge_nodes()
+    dof = (wn[:, :, None] * 3 + np.arange(3)).reshape(len(wn), 18)
+    A = sp.csr_matrix((element_matrices_hg(om.node_xyz()[wn], eta, hg).ravel(),
+                       (np.repeat(dof, 18, axis=1).ravel(), np.tile(dof, (1, 18)).ravel())))
+    keep = sp.diags(np.repeat(~om.boundary_nodes(), 3).astype(np.float64))
+    A = (keep @ A @ keep + sp.identity(A.shape[0]) - keep).tocsr()
+    rng = np.random.default_rng(4)
+    b, x = rng.standard_normal((2, om.n_nodes, 3))
+    eta_t = torch.tensor(eta[lm.wedge_index()], device="cuda").to(dt)
+    d = torch.empty((3,) + mesh.shape(0), dtype=dt, device="cuda")
+    tng.diag_A(ctx, mesh, 0, eta_t, d, hg_alpha=hg)
+    lib = [torch.tensor(lm.to_lib(v), device="cuda").to(dt).contiguous() for v in (b, x)]
+    tng.smooth(ctx, mesh, 0, eta_t, d, lib[0], lib[1], degree, 2, 0.3, 3.3, hg_alpha=hg)
+    torch.cuda.synchronize()
+    want = chebyshev(A, A.diagonal(), b.ravel(), x.ravel(), degree, 2, 0.3, 3.3).reshape(-1, 3)
+    got = lm.from_lib(lib[1].double().cpu().numpy(), check_dups=tol)
+    assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
