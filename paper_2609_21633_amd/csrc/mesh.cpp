@@ -292,10 +292,8 @@ void build_level(Level& L, int m, int n, double r_in, double r_out, bool device)
     L.owner.alloc(owner.size());
     TNG_HIP(hipMemcpy(L.owner.p, owner.data(), owner.size(), hipMemcpyHostToDevice));
     std::vector<double> im(10 * nl);
-    std::vector<float> im32(10 * nl);
     for (size_t q = 0; q < 10 * nl; ++q) {
         im[q] = group_of[q] < 0 ? 1.0 : 1.0 / (double)members[group_of[q]].size();
-        im32[q] = (float)im[q];
     }
     L.inv_mult64.alloc(im.size());
     TNG_HIP(hipMemcpy(L.inv_mult64.p, im.data(), im.size() * sizeof(double), hipMemcpyHostToDevice));
@@ -304,8 +302,6 @@ void build_level(Level& L, int m, int n, double r_in, double r_out, bool device)
     std::vector<float> u32(L.unit.begin(), L.unit.end());
     L.unit32.alloc(u32.size());
     TNG_HIP(hipMemcpy(L.unit32.p, u32.data(), u32.size() * sizeof(float), hipMemcpyHostToDevice));
-    L.inv_mult32.alloc(im32.size());
-    TNG_HIP(hipMemcpy(L.inv_mult32.p, im32.data(), im32.size() * sizeof(float), hipMemcpyHostToDevice));
 }
 
 }  // namespace

@@ -83,6 +83,13 @@ void vec_cheb_post_update(const tng_ctx* ctx, const Level& L, bool ns_in, bool n
 template <typename T>
 void vec_resid_post(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* b, const T* x, const T* y,
                     T* r);
+// z = invd A_D x from a raw viscous apply y = A x (closing pass fused, as above)
+template <typename T>
+void vec_mul_post(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* invd, const T* x, const T* y,
+                  T* z);
+// chebyshev_coefficients of the interval [lo, hi] * lambda into ab (device memory), lambda =
+// sqrt(pw[1] / pw[0]) from the squared norms of the last two power iterates
+void power_chebyshev(const tng_ctx* ctx, const double* pw, int deg, double lo, double hi, double* ab);
 // The same three uses of A_D x as one launch each (ring_smooth.hip), without hourglass
 // control and on levels where ring_apply_fits: a Chebyshev step, a residual, and a step of
 // the power iteration z = D^-1 A_D x.
@@ -106,6 +113,9 @@ void vec_axpby(const tng_ctx* ctx, long long n, double a, const T* x, double b, 
 template <typename T>
 void vec_mdot(const tng_ctx* ctx, DotScratch& ds, long long n, int n1, long long nlat, const uint8_t* owner,
               const T* x, const T* const* vs_dev, int nq, double* out_dev, bool accumulate);
+// o_c = a_c, c < 3, n values each
+template <typename T>
+void vec_copy3(const tng_ctx* ctx, long long n, const T* a0, const T* a1, const T* a2, T* o0, T* o1, T* o2);
 template <typename T>
 void vec_mul(const tng_ctx* ctx, long long n, const T* a, const T* b, T* c);
 template <typename T>

@@ -295,86 +295,75 @@ __global__ void __launch_bounds__(256) pmass_kernel(const T* __restrict__ eta, c
 // end nodes (edges along i, along j, or the split diagonal), radially odd
 // layers take the mean of the two coarse layers.  y += P x (add) or y = P x.
 template <typename T>
-__global__ void prolong_kernel(int mf, int nf, const T* __restrict__ c0, const T* __restrict__ c1,
-                               const T* __restrict__ c2, T* f0, T* f1, T* f2, int add, long long nslots,
-                               SlotBatch sb) {
+__global__ void __launch_bounds__(256) prolong_kernel(int mf, int nf, const T* __restrict__ c0,
+                                                      const T* __restrict__ c1, const T* __restrict__ c2, T* f0, T* f1,
+                                                      T* f2, int add, unsigned nslots, MagicDiv dn1, MagicDiv dm1,
+                                                      SlotBatch sb) {
     const long long so = slot_off(sb);
-    c0 = at_slot(c0, so);
-    c1 = at_slot(c1, so);
-    c2 = at_slot(c2, so);
-    f0 = at_slot(f0, so);
-    f1 = at_slot(f1, so);
-    f2 = at_slot(f2, so);
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
     if (t >= nslots) return;
-    const NodeIdx q = decode_node(t, mf, nf);
-    const int mc = mf / 2, nc = nf / 2;
-    int li[2], lj[2], nl;
-    if ((q.i & 1) == 0 && (q.j & 1) == 0) { li[0] = q.i / 2; lj[0] = q.j / 2; nl = 1; }
-    else if ((q.i & 1) && (q.j & 1) == 0) { li[0] = q.i / 2; lj[0] = q.j / 2; li[1] = q.i / 2 + 1; lj[1] = q.j / 2; nl = 2; }
-    else if ((q.i & 1) == 0 && (q.j & 1)) { li[0] = q.i / 2; lj[0] = q.j / 2; li[1] = q.i / 2; lj[1] = q.j / 2 + 1; nl = 2; }
-    else { li[0] = q.i / 2; lj[0] = q.j / 2 + 1; li[1] = q.i / 2 + 1; lj[1] = q.j / 2; nl = 2; }
-    int kr[2], nk;
-    if ((q.k & 1) == 0) { kr[0] = q.k / 2; nk = 1; } else { kr[0] = q.k / 2; kr[1] = q.k / 2 + 1; nk = 2; }
-    const T wl = nl == 1 ? T(1) : T(0.5), wk = nk == 1 ? T(1) : T(0.5);
-    T s[3] = {0, 0, 0};
-    const T* cs[3] = {c0, c1, c2};
-    for (int a = 0; a < nl; ++a)
-        for (int b = 0; b < nk; ++b) {
-            const long long ci = (((long long)q.d * (mc + 1) + li[a]) * (mc + 1) + lj[a]) * (nc + 1) + kr[b];
-            for (int c = 0; c < 3; ++c) s[c] += cs[c][ci];
-        }
-    T* fs[3] = {f0, f1, f2};
-    for (int c = 0; c < 3; ++c) {
-        const T v = s[c] * wl * wk;
-        fs[c][t] = add ? fs[c][t] + v : v;
-    }
+    const T* c = at_slot(blockIdx.y == 0 ? c0 : (blockIdx.y == 1 ? c1 : c2), so);
+    T* f = at_slot(blockIdx.y == 0 ? f0 : (blockIdx.y == 1 ? f1 : f2), so);
+    const T old = add ? f[t] : T(0);
+    const unsigned mf1 = mf + 1, nc1 = nf / 2 + 1, mc1 = mf / 2 + 1;
+    const unsigned lat = mdiv(t, dn1), k = t - lat * (nf + 1);
+    const unsigned row = mdiv(lat, dm1), j = lat - row * mf1;
+    const unsigned d = mdiv(row, dm1), i = row - d * mf1;
+    // the ends of the coarse edge the node lies on (the same node twice at a coarse node),
+    // and of the radial interval
+    const unsigned oi = i & 1, oj = j & 1;
+    const unsigned a = (d * mc1 + i / 2) * mc1 + j / 2 + (oi & oj);
+    const unsigned b = a + (oi ? mc1 : 0u) + (oi & oj ? 0u - 1u : oj);
+    const unsigned ok = k & 1, ka = k / 2;
+    const T* ca = c + (size_t)a * nc1 + ka;
+    const T* cb = c + (size_t)b * nc1 + ka;
+    const T v = T(0.25) * ((ca[0] + cb[0]) + (ca[ok] + cb[ok]));
+    f[t] = add ? old + v : v;
 }
 
-// Restriction R = P^T, per diamond: a coarse node gathers the fine nodes it
-// interpolates to, each weighted by its interpolation weight and by
-// 1/multiplicity of the fine node (so the interface sum over diamond copies
-// counts every fine node once).  No-slip layers of the result are zero; the layer of
-// a free-slip sphere (fs bit 0 inner, bit 1 outer) is restricted like the interior.
+// Restriction R = P^T: a coarse node gathers the fine nodes that interpolate from it, the
+// fine node at its place (weight 1) and that node's ring of neighbours (1/2 each: the
+// midpoints of the coarse edges at the node, over all diamonds, so that no interface sum
+// follows), on three fine layers (1/2, 1, 1/2).  No-slip layers of the result are zero; the
+// layer of a free-slip sphere (fs bit 0 inner, bit 1 outer) is restricted like the interior.
 template <typename T>
-__global__ void restrict_kernel(int mf, int nf, const T* __restrict__ f0, const T* __restrict__ f1,
-                                const T* __restrict__ f2, const T* __restrict__ inv_mult,
-                                T* c0, T* c1, T* c2, long long ncslots, int fs, SlotBatch sb) {
+__global__ void __launch_bounds__(256) restrict_kernel(int mf, int nf, const T* __restrict__ f0,
+                                                       const T* __restrict__ f1, const T* __restrict__ f2,
+                                                       const int* __restrict__ ring_tri,
+                                                       const int* __restrict__ ring_nb, T* c0, T* c1, T* c2,
+                                                       unsigned ncslots, MagicDiv dn1, MagicDiv dm1, int fs,
+                                                       SlotBatch sb) {
     const long long so = slot_off(sb);
-    f0 = at_slot(f0, so);
-    f1 = at_slot(f1, so);
-    f2 = at_slot(f2, so);
-    c0 = at_slot(c0, so);
-    c1 = at_slot(c1, so);
-    c2 = at_slot(c2, so);
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
     if (t >= ncslots) return;
-    const int mc = mf / 2, nc = nf / 2;
-    const NodeIdx q = decode_node(t, mc, nc);
-    T s[3] = {0, 0, 0};
-    if ((q.k > 0 || (fs & 1)) && (q.k < nc || (fs & 2))) {
-        // lateral fine neighbours that interpolate from this coarse node
-        const int di[7] = {0, 1, -1, 0, 0, 1, -1};
-        const int dj[7] = {0, 0, 0, 1, -1, -1, 1};
-        const T wl[7] = {T(1), T(0.5), T(0.5), T(0.5), T(0.5), T(0.5), T(0.5)};
-        const T* fs[3] = {f0, f1, f2};
-        for (int l = 0; l < 7; ++l) {
-            const int fi = 2 * q.i + di[l], fj = 2 * q.j + dj[l];
-            if (fi < 0 || fi > mf || fj < 0 || fj > mf) continue;
-            const long long lat = ((long long)q.d * (mf + 1) + fi) * (mf + 1) + fj;
-            const T wm = wl[l] * inv_mult[lat];
-            for (int dk = -1; dk <= 1; ++dk) {
-                const int fk = 2 * q.k + dk;
-                if (fk < 0 || fk > nf) continue;
-                const T w = dk == 0 ? wm : T(0.5) * wm;
-                const long long fidx = lat * (nf + 1) + fk;
-                for (int c = 0; c < 3; ++c) s[c] += w * fs[c][fidx];
-            }
+    const T* f = at_slot(blockIdx.y == 0 ? f0 : (blockIdx.y == 1 ? f1 : f2), so);
+    T* c = at_slot(blockIdx.y == 0 ? c0 : (blockIdx.y == 1 ? c1 : c2), so);
+    const unsigned mc1 = mf / 2 + 1, nc = nf / 2;
+    const unsigned lat = mdiv(t, dn1), k = t - lat * (nc + 1);
+    T v = T(0);
+    if ((k > 0 || (fs & 1)) && (k < nc || (fs & 2))) {
+        const unsigned row = mdiv(lat, dm1), j = lat - row * mc1;      // row = d (mc + 1) + i
+        const unsigned d = mdiv(row, dm1), i = row - d * mc1;
+        const unsigned fl = (d * (mf + 1) + 2 * i) * (mf + 1) + 2 * j;
+        const bool five = ring_tri[fl * 6 + 5] < 0;
+        const unsigned kb = k > 0 ? 2 * k - 1 : 0, kt = k < nc ? 2 * k + 1 : 2 * nc;
+        const T wb = k > 0 ? T(0.5) : T(0), wt = k < nc ? T(0.5) : T(0);
+        T p[7][3];
+#pragma unroll
+        for (int r = 0; r < 7; ++r) {
+            const T* q = f + (size_t)(r < 6 ? (unsigned)ring_nb[fl * 6 + r] : fl) * (nf + 1);
+            p[r][0] = q[kb];
+            p[r][1] = q[2 * k];
+            p[r][2] = q[kt];
         }
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            const T s = p[r][1] + (wb * p[r][0] + wt * p[r][2]);
+            v += r == 5 && five ? T(0) : s;
+        }
+        v = T(0.5) * v + (p[6][1] + (wb * p[6][0] + wt * p[6][2]));
     }
-    c0[t] = s[0];
-    c1[t] = s[1];
-    c2[t] = s[2];
+    c[t] = v;
 }
 
 // One Chebyshev step of the smoother on D^{-1} A, fused after y = A x:
@@ -638,8 +627,9 @@ __global__ void __launch_bounds__(256) axpby_kernel(long long n, T a, const T* _
 constexpr int DOT_BS = 256;
 
 // Residual r = b - A_D x from a raw viscous apply y (the closing pass fused as in
-// cheb_post_update_kernel: copies summed in group order, identity rows r = b - x).
-template <typename T>
+// cheb_post_update_kernel: copies summed in group order, identity rows r = b - x); MUL: the
+// step r = b A_D x of the power iteration, b the inverse diagonal.
+template <typename T, bool MUL>
 __global__ void __launch_bounds__(256) resid_post_kernel(int ns, int n1, MagicDiv dn1, const int* __restrict__ lat_grp,
                                                         const int* __restrict__ gp, const int* __restrict__ gs,
                                                         int ns_in, int ns_out, const T* __restrict__ b,
@@ -664,7 +654,8 @@ __global__ void __launch_bounds__(256) resid_post_kernel(int ns, int n1, MagicDi
             for (int q = s0 + 1; q < s1; ++q) yv += yy[(long long)gs[q] * n1 + kk];
         }
     }
-    at_slot(r, so)[e] = at_slot(b, so)[e] - yv;
+    const T bv = at_slot(b, so)[e];
+    at_slot(r, so)[e] = MUL ? bv * yv : bv - yv;
 }
 
 // One Chebyshev step of the smoother in its two-term form
@@ -886,6 +877,14 @@ __global__ void __launch_bounds__(256) maxpy_kernel(unsigned n, const double* __
             y[t] = T(acc);
         }
     }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) copy3_kernel(unsigned n, const T* a0, const T* a1, const T* a2, T* o0, T* o1,
+                                                    T* o2) {
+    const T* a = blockIdx.y == 0 ? a0 : (blockIdx.y == 1 ? a1 : a2);
+    T* o = blockIdx.y == 0 ? o0 : (blockIdx.y == 1 ? o1 : o2);
+    for (unsigned t = blockIdx.x * 256u + threadIdx.x; t < n; t += gridDim.x * 256u) o[t] = a[t];
 }
 
 template <typename T>
@@ -1554,8 +1553,9 @@ template <typename T>
 void mg_prolong(const tng_ctx* ctx, const Level& Lf, const T* const c[3], T* const f[3], bool add) {
     const long long ns = Lf.node_slots();
     const SlotBatch sb = launch_batch();
-    prolong_kernel<T><<<dim3(nblk(ns, 256), 1, sb.nb), 256, 0, ctx->stream>>>(Lf.m, Lf.n, c[0], c[1], c[2], f[0],
-                                                                              f[1], f[2], add ? 1 : 0, ns, sb);
+    prolong_kernel<T><<<dim3(nblk(ns, 256), 3, sb.nb), 256, 0, ctx->stream>>>(
+        Lf.m, Lf.n, c[0], c[1], c[2], f[0], f[1], f[2], add ? 1 : 0, (unsigned)ns, magic_div((unsigned)(Lf.n + 1)),
+        magic_div((unsigned)(Lf.m + 1)), sb);
     TNG_HIP(hipGetLastError());
 }
 
@@ -1563,13 +1563,11 @@ template <typename T>
 void mg_restrict(const tng_ctx* ctx, const Level& Lf, const Level& Lc, const T* const f[3], T* const c[3],
                  unsigned fs) {
     const long long ns = Lc.node_slots();
-    const T* im = std::is_same<T, double>::value ? (const T*)Lf.inv_mult64.p : (const T*)Lf.inv_mult32.p;
     const SlotBatch sb = launch_batch();
-    restrict_kernel<T><<<dim3(nblk(ns, 256), 1, sb.nb), 256, 0, ctx->stream>>>(Lf.m, Lf.n, f[0], f[1], f[2], im,
-                                                                               c[0], c[1], c[2], ns, (int)fs, sb);
+    restrict_kernel<T><<<dim3(nblk(ns, 256), 3, sb.nb), 256, 0, ctx->stream>>>(
+        Lf.m, Lf.n, f[0], f[1], f[2], Lf.ring_tri.p, Lf.ring_nb.p, c[0], c[1], c[2], (unsigned)ns,
+        magic_div((unsigned)(Lc.n + 1)), magic_div((unsigned)(Lc.m + 1)), (int)fs, sb);
     TNG_HIP(hipGetLastError());
-    void* g[3] = {c[0], c[1], c[2]};
-    launch_interface(ctx, Lc, prec_of<T>(), 0, 3, g);
     if (fs) vec_fs_project<T>(ctx, Lc, fs, c, nullptr);
 }
 
@@ -1616,14 +1614,49 @@ void vec_cheb_post_update(const tng_ctx* ctx, const Level& L, bool ns_in, bool n
     TNG_HIP(hipGetLastError());
 }
 
+template <typename T, bool MUL>
+void launch_resid_post(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* b, const T* x, const T* y,
+                       T* r) {
+    const SlotBatch sb = launch_batch();
+    const long long ns = L.node_slots();
+    resid_post_kernel<T, MUL><<<dim3(std::max(1u, nblk(ns, 256)), 3, sb.nb), 256, 0, ctx->stream>>>(
+        (int)ns, L.n + 1, magic_div((unsigned)(L.n + 1)), L.lat_grp.p, L.grp_ptr.p, L.grp_slot.p, ns_in ? 1 : 0,
+        ns_out ? 1 : 0, b, x, y, r, sb);
+    TNG_HIP(hipGetLastError());
+}
+
 template <typename T>
 void vec_resid_post(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* b, const T* x, const T* y,
                     T* r) {
-    const SlotBatch sb = launch_batch();
-    const long long ns = L.node_slots();
-    resid_post_kernel<T><<<dim3(std::max(1u, nblk(ns, 256)), 3, sb.nb), 256, 0, ctx->stream>>>(
-        (int)ns, L.n + 1, magic_div((unsigned)(L.n + 1)), L.lat_grp.p, L.grp_ptr.p, L.grp_slot.p, ns_in ? 1 : 0,
-        ns_out ? 1 : 0, b, x, y, r, sb);
+    launch_resid_post<T, false>(ctx, L, ns_in, ns_out, b, x, y, r);
+}
+
+template <typename T>
+void vec_mul_post(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* invd, const T* x, const T* y,
+                  T* z) {
+    launch_resid_post<T, true>(ctx, L, ns_in, ns_out, invd, x, y, z);
+}
+
+// Chebyshev coefficients on the device (the arithmetic of chebyshev_coefficients)
+__global__ void power_chebyshev_kernel(const double* __restrict__ pw, int deg, double lo, double hi, double* ab) {
+    if (threadIdx.x != 0) return;
+    const double lam = sqrt(pw[1]) / sqrt(pw[0]);
+    const double l = lo * lam, h = hi * lam;
+    const double theta = 0.5 * (h + l), delta = 0.5 * (h - l), sigma = theta / delta;
+    ab[0] = 0.0;
+    ab[1] = 1.0 / theta;
+    double rho_old = 1.0 / sigma;
+    for (int k = 1; k < deg; ++k) {
+        const double rho = 1.0 / (2.0 * sigma - rho_old);
+        ab[2 * k] = rho * rho_old;
+        ab[2 * k + 1] = 2.0 * rho / delta;
+        rho_old = rho;
+    }
+}
+
+void power_chebyshev(const tng_ctx* ctx, const double* pw, int deg, double lo, double hi, double* ab) {
+    require_unbatched("power_chebyshev");
+    power_chebyshev_kernel<<<1, 64, 0, ctx->stream>>>(pw, deg, lo, hi, ab);
     TNG_HIP(hipGetLastError());
 }
 
@@ -1838,6 +1871,14 @@ void coarse_assemble(const tng_ctx* ctx, CoarseDense& cd, const Level& L, const 
 }
 
 template <typename T>
+void vec_copy3(const tng_ctx* ctx, long long n, const T* a0, const T* a1, const T* a2, T* o0, T* o1, T* o2) {
+    require_unbatched("vec_copy3");
+    const unsigned nb = (unsigned)std::min<long long>(nblk(n, 256), 8192);
+    copy3_kernel<T><<<dim3(nb, 3), 256, 0, ctx->stream>>>((unsigned)n, a0, a1, a2, o0, o1, o2);
+    TNG_HIP(hipGetLastError());
+}
+
+template <typename T>
 void vec_mul(const tng_ctx* ctx, long long n, const T* a, const T* b, T* c) {
     require_unbatched("vec_mul");
     const unsigned nb = (unsigned)std::min<long long>(nblk(n, 256), 8192);
@@ -1916,6 +1957,7 @@ void vec_schur(const tng_ctx* ctx, long long n, const T* r, const T* mdiag, T* z
     template void mg_restrict<T>(const tng_ctx*, const Level&, const Level&, const T* const[3],           \
                                  T* const[3], unsigned);                                                   \
     template void vec_resid_post<T>(const tng_ctx*, const Level&, bool, bool, const T*, const T*, const T*, T*); \
+    template void vec_mul_post<T>(const tng_ctx*, const Level&, bool, bool, const T*, const T*, const T*, T*);   \
     template void vec_cheb_post_update<T>(const tng_ctx*, const Level&, bool, bool, const double*, int, bool,   \
                                           bool, const T*, const T*, const T*, const T*, T*);                 \
     template void vec_cheb_update<T>(const tng_ctx*, long long, const double*, int, const T*, const T*,   \
@@ -1929,6 +1971,7 @@ void vec_schur(const tng_ctx* ctx, long long n, const T* r, const T* mdiag, T* z
     template void vec_schur<T>(const tng_ctx*, long long, const T*, const T*, T*);                       \
     template void vec_maxpy<T>(const tng_ctx*, long long, const double*, double, const T* const*, int, T*); \
     template void vec_fill<T>(const tng_ctx*, long long, T, T*);                                          \
+    template void vec_copy3<T>(const tng_ctx*, long long, const T*, const T*, const T*, T*, T*, T*);         \
     template void vec_mul<T>(const tng_ctx*, long long, const T*, const T*, T*);                          \
     template void vec_smdot<T>(const tng_ctx*, DotScratch&, const Level&, const Level&, const T*,         \
                                const T* const*, int, double*, bool, bool);                                 \

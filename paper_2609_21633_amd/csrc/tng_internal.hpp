@@ -211,7 +211,6 @@ struct Level {
     DevBuf<float> unit32;
     DevBuf<double> rho64;             // [n+1] reference density at the node layers (TALA), if set
     DevBuf<float> rho32;
-    DevBuf<float> inv_mult32;
 
     long long lat_slots() const { return 10LL * (m + 1) * (m + 1); }
     long long node_slots() const { return lat_slots() * (n + 1); }

@@ -146,3 +146,28 @@ def test_smoother(tng, ctx, dtype, tol, mt, nr, degree, hg):
     want = chebyshev(A, A.diagonal(), b.ravel(), x.ravel(), degree, 2, 0.3, 3.3).reshape(-1, 3)
     got = lm.from_lib(lib[1].double().cpu().numpy(), check_dups=tol)
     assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("dtype,tol", [("float64", 1e-13), ("float32", 1e-6)])
+@pytest.mark.parametrize("mt,nr", [(2, 2), (4, 6), (2, 130), (8, 62)])
+def test_transfers(tng, ctx, dtype, tol, mt, nr):
+    """Restriction over the fine ring and prolongation against the oracle's P: weighted sums of
+    at most 21 values, in FP32 a few roundings of 6e-8."""
+    import torch
+    dt = getattr(torch, dtype)
+    mesh, om, omp, lm, lmp, eta, orc = shell(tng, ctx, mt, nr)
+    rng = np.random.default_rng(3)
+    f, c = rng.standard_normal((om.n_nodes, 3)), rng.standard_normal((omp.n_nodes, 3))
+    ct = torch.full((3,) + mesh.shape(1), float("nan"), dtype=dt, device="cuda")
+    ft = torch.full((3,) + mesh.shape(0), float("nan"), dtype=dt, device="cuda")
+    tng.restrict(ctx, mesh, 0, torch.tensor(lm.to_lib(f), device="cuda").to(dt).contiguous(), ct)
+    tng.prolong(ctx, mesh, 0, torch.tensor(lmp.to_lib(c), device="cuda").to(dt).contiguous(), ft)
+    torch.cuda.synchronize()
+    P = velocity_prolongation(orc)
+    want_c = (P.T @ f.ravel()).reshape(-1, 3)
+    want_c[omp.boundary_nodes()] = 0.0
+    want_f = (P @ c.ravel()).reshape(-1, 3)
+    got_c = lmp.from_lib(ct.double().cpu().numpy(), check_dups=1e-15)
+    got_f = lm.from_lib(ft.double().cpu().numpy(), check_dups=1e-15)
+    assert np.linalg.norm(got_c - want_c) <= tol * np.linalg.norm(want_c)
+    assert np.linalg.norm(got_f - want_f) <= tol * np.linalg.norm(want_f)
