@@ -308,9 +308,9 @@ int tng_prolong(tng_ctx* ctx, const tng_mesh* mesh, int fine_level, tng_prec pre
  *   iteration limit per refinement step, and the refinement step limit.
  * hg_alpha: hourglass control (eq:hgstab, see tng_stokes_apply) of the viscous
  *   block on every level: the solve is then of that stabilised operator.
- * graphs: 1 (default) replays the preconditioner of each Krylov index as a
- *   HIP graph captured at its first use (on a private stream ordered with the
- *   context's stream by events); 0 launches every kernel from the host.
+ * graphs: 0 or 1 (default), of no effect: every kernel is launched from the host
+ *   (the preconditioner of each Krylov index replayed as a captured HIP graph
+ *   was measured 1 to 20 % slower at every size).
  * op_flags: operator variant of the solve (Sec. 4, eq:stokes), 0 (default) or
  *   one of
  *   TNG_OP_TWOPOINT: the viscous block with the two-radial-point rule on every

@@ -29,10 +29,8 @@ struct MGLevel {
     DevBuf<T> eta;                      // wedge viscosity of this level
     DevBuf<T> invd;                     // 3 ns: inverse diagonal of A
     DevBuf<T> x, b, r, y, d;            // 3 ns scratch
-    DevBuf<const T*> xy;                // device pointers {x, y} for reductions
+    DevBuf<const T*> xd;                // device pointers {x, d} for reductions
     DevBuf<double> cheb;                // Chebyshev coefficients (alpha_k, beta_k) of this level
-    std::vector<double> cheb_h;         //   host copy (kept until the upload has run)
-    double lmax = 1.0;                  // largest eigenvalue of D^{-1} A (estimate)
     T* c(DevBuf<T>& v, int k) { return v.p + (long long)k * ns; }
 };
 
@@ -82,6 +80,7 @@ struct tng_solver {
     bool fp64_inner = false, fp64_ops = false;
     tng::DevBuf<double> d64;
     tng::DevBuf<double> scal;           // device scalars
+    tng::DevBuf<double> pw;             // per level: squared norms of the last two power iterates
     tng::DevBuf<const double*> dptr;    // [bo, ro, pressure of xo, k64.w]
     double* host = nullptr;             // pinned read-back buffer
     bool ready = false;
@@ -89,23 +88,7 @@ struct tng_solver {
     long long ns0 = 0, np = 0, N = 0;
     tng::EnergyWS* ews = nullptr;       // energy step workspace (created on first use)
     tng::DevBuf<double> eta_step, f_step;
-    // preconditioner graphs: z_j = P^{-1} v_j of Krylov index j, captured on a
-    // private stream (gctx) at first use and replayed there, ordered with the
-    // context's stream by the events
-    hipStream_t gstream = nullptr;
-    tng_ctx* gctx = nullptr;
-    hipEvent_t ev_in = nullptr, ev_out = nullptr;
-    std::vector<hipGraphExec_t> pg32, pg64;
     ~tng_solver() {
-        if (gstream) (void)hipStreamSynchronize(gstream);
-        for (auto g : pg32)
-            if (g) (void)hipGraphExecDestroy(g);
-        for (auto g : pg64)
-            if (g) (void)hipGraphExecDestroy(g);
-        if (ev_in) (void)hipEventDestroy(ev_in);
-        if (ev_out) (void)hipEventDestroy(ev_out);
-        if (gctx) tng_ctx_destroy(gctx);
-        if (gstream) (void)hipStreamDestroy(gstream);
         if (host) (void)hipHostFree(host);
         if (ews) tng::energy_ws_destroy(ews);
     }
@@ -386,51 +369,27 @@ void precond(tng_solver* s, const T* v, T* z) {
     project_rotations<T>(s, z);
 }
 
+// One V-cycle on the caller's velocity fields: straight on them when their components
+// follow one another as in the solver's vectors, 16-byte aligned and without overlap
+// ((128,128) FP32: 0.2 ms of copies less), else through copies.  Launched from the host:
+// replayed as a graph the cycle is slower at every size ((8,8) FP64 94 -> 145 us, (32,32)
+// 464 -> 541 us: about 1.5 us more between two kernels).
 template <typename T>
-std::vector<hipGraphExec_t>& pgraphs(tng_solver* s);
-template <>
-std::vector<hipGraphExec_t>& pgraphs<float>(tng_solver* s) { return s->pg32; }
-template <>
-std::vector<hipGraphExec_t>& pgraphs<double>(tng_solver* s) { return s->pg64; }
-
-// Z_j = P^{-1} V_j, as a replayed graph when the solver has graphs
-template <typename T>
-void precond_j(tng_solver* s, int j) {
-    KrylovWS<T>& K = kws<T>(s);
-    if (!s->gctx) {
-        precond<T>(s, K.Vi(j), K.Zi(j));
+void vcycle_fields(tng_solver* s, const T* const b[3], T* const x[3]) {
+    const long long ns = s->ns0, n3 = 3 * ns;
+    const auto u = [](const T* p) { return reinterpret_cast<uintptr_t>(p); };
+    const bool flat = b[1] == b[0] + ns && b[2] == b[0] + 2 * ns && x[1] == x[0] + ns && x[2] == x[0] + 2 * ns &&
+                      u(b[0]) % 16 == 0 && u(x[0]) % 16 == 0 &&
+                      (u(b[0]) + n3 * sizeof(T) <= u(x[0]) || u(x[0]) + n3 * sizeof(T) <= u(b[0]));
+    if (flat) {
+        vcycle<T>(s, 0, b[0], x[0]);
         return;
     }
-    auto& G = pgraphs<T>(s);
-    if (G.size() < (size_t)K.restart) G.assign(K.restart, nullptr);
-    if (!G[j]) {
-        // capture with every launch on the private stream; no timers inside
-        tng_ctx* saved = s->ctx;
-        hipGraph_t graph = nullptr;
-        TNG_HIP(hipStreamBeginCapture(s->gstream, hipStreamCaptureModeThreadLocal));
-        s->ctx = s->gctx;
-        try {
-            precond<T>(s, K.Vi(j), K.Zi(j));
-        } catch (...) {
-            s->ctx = saved;
-            (void)hipStreamEndCapture(s->gstream, &graph);
-            if (graph) (void)hipGraphDestroy(graph);
-            throw;
-        }
-        s->ctx = saved;
-        TNG_HIP(hipStreamEndCapture(s->gstream, &graph));
-        const hipError_t e = hipGraphInstantiate(&G[j], graph, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(graph);
-        if (e != hipSuccess) {
-            G[j] = nullptr;
-            throw Error(TNG_E_HIP, std::string("preconditioner graph: ") + hipGetErrorString(e));
-        }
-    }
-    TNG_HIP(hipEventRecord(s->ev_in, s->ctx->stream));
-    TNG_HIP(hipStreamWaitEvent(s->gstream, s->ev_in, 0));
-    TNG_HIP(hipGraphLaunch(G[j], s->gstream));
-    TNG_HIP(hipEventRecord(s->ev_out, s->gstream));
-    TNG_HIP(hipStreamWaitEvent(s->ctx->stream, s->ev_out, 0));
+    T* bi = hier<T>(s)[0].b.p;
+    T* xi = kws<T>(s).t.p;
+    vec_copy3<T>(s->ctx, ns, b[0], b[1], b[2], bi, bi + ns, bi + 2 * ns);
+    vcycle<T>(s, 0, bi, xi);
+    vec_copy3<T>(s->ctx, ns, xi, xi + ns, xi + 2 * ns, x[0], x[1], x[2]);
 }
 
 double host_norm_from_dev(tng_solver* s, const double* dev) {
@@ -470,7 +429,7 @@ int fgmres(tng_solver* s, const T* eta0, const T* b, T* x, double rtol, int maxi
         g[0] = beta;
         int jend = 0;
         for (int j = 0; j < m; ++j) {
-            precond_j<T>(s, j);
+            precond<T>(s, K.Vi(j), K.Zi(j));
             apply_K<T>(s, eta0, K.Zi(j), K.w.p);
             // classical Gram-Schmidt, twice: h1 = V^T w; w -= V h1 with h2 = V^T w in the
             // same pass; w -= V h2 with |w|^2 in the same pass
@@ -615,9 +574,9 @@ void alloc_level_scratch(tng_solver* s, MGLevel<T>& M) {
     M.y.alloc(n3);
     M.d.alloc(n3);
     M.cheb.alloc(2 * (size_t)std::max(1, s->opts.cheb_degree));
-    const T* xy[2] = {M.x.p, M.y.p};
-    M.xy.alloc(2);
-    TNG_HIP(hipMemcpy(M.xy.p, xy, sizeof(xy), hipMemcpyHostToDevice));
+    const T* xd[2] = {M.x.p, M.d.p};
+    M.xd.alloc(2);
+    TNG_HIP(hipMemcpy(M.xd.p, xd, sizeof(xd), hipMemcpyHostToDevice));
 }
 
 template <typename T>
@@ -647,37 +606,69 @@ void alloc_krylov(tng_solver* s, const T* rhs) {
     TNG_HIP(hipMemcpy(K.wptr.p, wp.data(), wp.size() * sizeof(T*), hipMemcpyHostToDevice));
 }
 
-// largest eigenvalue of D^{-1} A on level l by seeded power iteration
+// Chebyshev coefficients of level l from the largest eigenvalue of D^{-1} A, estimated by
+// power_its seeded power iterations.  Nothing is read back: the squared norms of the last
+// two iterates stay in s->pw[2 l], s->pw[2 l + 1] (check_power looks at them once all
+// levels are enqueued) and the coefficients are formed on the device.  The iterate is
+// normalised every POWER_NORM iterations only, which FP32 holds easily (the eigenvalues of
+// D^{-1} A are of order one).
+constexpr int POWER_NORM = 8;
+
 template <typename T>
-double power_lmax(tng_solver* s, int l) {
+void power_cheb(tng_solver* s, int l) {
     MGLevel<T>& M = hier<T>(s)[l];
-    const long long n3 = 3 * M.ns;
+    const Level& L = *M.L;
+    const long long ns = M.ns, n3 = 3 * ns;
     vec_rand<T>(s->ctx, n3, 0x5eed0000ULL + (unsigned long long)l, M.x.p);
     {
-        void* f[3] = {M.x.p, M.x.p + M.ns, M.x.p + 2 * M.ns};
-        launch_interface(s->ctx, *M.L, prec_of<T>(), 1, 3, f);
+        void* f[3] = {M.x.p, M.x.p + ns, M.x.p + 2 * ns};
+        launch_interface(s->ctx, L, prec_of<T>(), 1, 3, f);
     }
     // free slip: the normal rows of D^{-1} (P A P + N) have eigenvalue 1 / d, outside
     // the smoother's spectrum; the iteration stays tangential there
-    T* xv[3] = {M.x.p, M.x.p + M.ns, M.x.p + 2 * M.ns};
-    T* yv[3] = {M.y.p, M.y.p + M.ns, M.y.p + 2 * M.ns};
-    vec_fs_project<T>(s->ctx, *M.L, fs_bits(s), xv, nullptr);
-    const T* const* xp = M.xy.p;
-    const T* const* yp = M.xy.p + 1;
-    double lam = 1.0;
+    T* xv[3] = {M.x.p, M.x.p + ns, M.x.p + 2 * ns};
+    vec_fs_project<T>(s->ctx, L, fs_bits(s), xv, nullptr);
+    double* pw = s->pw.p + 2 * l;
+    const bool ring = !fs_flag(s) && !twopt_flag(s) && s->opts.hg_alpha == 0.0 && ring_apply_fits<T>(L);
+    int cur = 0;                                     // the iterate: M.x (0) or M.d (1), also in M.xd
+    auto norm2 = [&](int which, double* out) {
+        vel_dot<T>(s, l, which ? M.d.p : M.x.p, M.xd.p + which, out);
+    };
     for (int it = 0; it < s->opts.power_its; ++it) {
-        apply_A<T>(s, l, M.eta.p, M.x.p, M.y.p);
-        vec_mul<T>(s->ctx, n3, M.invd.p, M.y.p, M.y.p);
-        vec_fs_project<T>(s->ctx, *M.L, fs_bits(s), yv, nullptr);
-        vel_dot<T>(s, l, M.x.p, xp, s->scal.p);
-        vel_dot<T>(s, l, M.y.p, yp, s->scal.p + 1);
-        readback(s, s->scal.p, 2);
-        const double nx = std::sqrt(s->host[0]), ny = std::sqrt(s->host[1]);
-        if (!(nx > 0) || !std::isfinite(ny)) throw Error(TNG_E_NOTCONV, "power iteration failed");
-        lam = ny / nx;
-        vec_axpby<T>(s->ctx, n3, 1.0 / ny, M.y.p, 0.0, M.x.p);
+        T* x = cur ? M.d.p : M.x.p;
+        T* z = cur ? M.x.p : M.d.p;
+        const bool last = it + 1 == s->opts.power_its;
+        if (last) norm2(cur, pw);
+        // z = D^{-1} A x
+        if (ring) {
+            ring_power<T>(s->ctx, L, true, true, M.eta.p, M.invd.p, x, z);
+        } else if (fs_flag(s)) {
+            apply_A<T>(s, l, M.eta.p, x, M.y.p);
+            vec_mul<T>(s->ctx, n3, M.invd.p, M.y.p, z);
+            T* zv[3] = {z, z + ns, z + 2 * ns};
+            vec_fs_project<T>(s->ctx, L, fs_bits(s), zv, nullptr);
+        } else {
+            const void* u[3] = {x, x + ns, x + 2 * ns};
+            void* yu[3] = {M.y.p, M.y.p + ns, M.y.p + 2 * ns};
+            launch_stokes_apply_raw(s->ctx, L, prec_of<T>(), TNG_OP_A | TNG_OP_DIRICHLET | twopt_flag(s),
+                                    s->opts.hg_alpha, M.eta.p, u, yu);
+            vec_mul_post<T>(s->ctx, L, true, true, M.invd.p, x, M.y.p, z);
+        }
+        cur ^= 1;
+        if (last || (it + 1) % POWER_NORM == 0) norm2(cur, pw + 1);
+        if (!last && (it + 1) % POWER_NORM == 0) vec_scale_rsqrt<T>(s->ctx, n3, pw + 1, z, z);
     }
-    return lam;
+    power_chebyshev(s->ctx, pw, std::max(1, s->opts.cheb_degree), s->opts.cheb_lo, s->opts.cheb_hi, M.cheb.p);
+}
+
+// Waits for a set-up and fails if a power iteration met a zero or non-finite iterate.
+void check_power(tng_solver* s) {
+    readback(s, s->pw.p, 2 * (s->nlev - 1));
+    for (int l = 0; l < s->nlev - 1; ++l) {
+        const double nx = std::sqrt(s->host[2 * l]), ny = std::sqrt(s->host[2 * l + 1]);
+        if (!(nx > 0) || !std::isfinite(nx) || !std::isfinite(ny))
+            throw Error(TNG_E_NOTCONV, "power iteration failed");
+    }
 }
 
 template <typename T>
@@ -687,10 +678,7 @@ void setup_level_operators(tng_solver* s) {
         MGLevel<T>& M = H[l];
         T* d[3] = {M.invd.p, M.invd.p + M.ns, M.invd.p + 2 * M.ns};
         mg_diag_A<T>(s->ctx, *M.L, M.eta.p, s->opts.hg_alpha, d, twopt_flag(s) != 0, fs_bits(s), true);
-        M.lmax = power_lmax<T>(s, l);
-        M.cheb_h = chebyshev_coefficients(std::max(1, s->opts.cheb_degree), s->opts.cheb_lo * M.lmax,
-                                          s->opts.cheb_hi * M.lmax);
-        M.cheb.upload(M.cheb_h.data(), M.cheb_h.size(), s->ctx->stream);
+        power_cheb<T>(s, l);
     }
 }
 
@@ -715,7 +703,7 @@ void setup_viscosity(tng_solver* s, const double* eta_dev) {
         vec_cast<float, double>(s->ctx, s->np, s->pm64.p, s->pm32.p);
         setup_level_operators<float>(s);
     }
-    sync(s);
+    check_power(s);
     s->ready = true;
 }
 
@@ -733,7 +721,7 @@ void enable_fp64_inner(tng_solver* s) {
     }
     if (!s->fp64_ops) {
         setup_level_operators<double>(s);
-        sync(s);
+        check_power(s);
         s->fp64_ops = true;
     }
 }
@@ -1413,6 +1401,7 @@ tng_solver* create_solver(tng_ctx* ctx, tng_mesh* mesh, const tng_solver_opts* o
         TNG_HIP(hipMemcpy(s->onesp32.p, &o32, sizeof(o32), hipMemcpyHostToDevice));
     }
     s->scal.alloc(64);
+    s->pw.alloc(2 * (size_t)nlev);
     {
         const double* dp[4] = {s->bo.p, s->ro.p, s->xo.p + 3 * s->ns0, s->k64.w.p};
         s->dptr.alloc(4);
@@ -1464,13 +1453,6 @@ tng_solver* create_solver(tng_ctx* ctx, tng_mesh* mesh, const tng_solver_opts* o
         TNG_HIP(hipMemcpy(s->rotptr32.p, rp32, sizeof(rp32), hipMemcpyHostToDevice));
     }
     TNG_HIP(hipHostMalloc(reinterpret_cast<void**>(&s->host), 256 * sizeof(double), hipHostMallocDefault));
-    if (opts->graphs && !batch_slot) {
-        TNG_HIP(hipStreamCreateWithFlags(&s->gstream, hipStreamNonBlocking));   // default priority
-        if (tng_ctx_create(ctx->device, s->gstream, &s->gctx) != TNG_OK)
-            throw Error(TNG_E_HIP, "graph context creation failed");
-        TNG_HIP(hipEventCreateWithFlags(&s->ev_in, hipEventDisableTiming));
-        TNG_HIP(hipEventCreateWithFlags(&s->ev_out, hipEventDisableTiming));
-    }
     TNG_HIP(hipStreamSynchronize(ctx->stream));
     return s.release();
 }
@@ -1694,22 +1676,14 @@ int tng_stokes_solver_vcycle(tng_solver* s, const void* const b[3], void* const 
         tng::require_device(s->ctx, x[c], vb, "x");
     }
     TNG_HIP(hipSetDevice(s->ctx->device));
-    const long long ns = s->ns0;
-    hipStream_t st = s->ctx->stream;
     if (s->opts.mixed) {
-        auto& M = s->h32[0];
-        for (int c = 0; c < 3; ++c)
-            TNG_HIP(hipMemcpyAsync(M.b.p + c * ns, b[c], ns * sizeof(float), hipMemcpyDeviceToDevice, st));
-        tng::vcycle<float>(s, 0, M.b.p, s->k32.t.p);
-        for (int c = 0; c < 3; ++c)
-            TNG_HIP(hipMemcpyAsync(x[c], s->k32.t.p + c * ns, ns * sizeof(float), hipMemcpyDeviceToDevice, st));
+        const float* bf[3] = {(const float*)b[0], (const float*)b[1], (const float*)b[2]};
+        float* xf[3] = {(float*)x[0], (float*)x[1], (float*)x[2]};
+        tng::vcycle_fields<float>(s, bf, xf);
     } else {
-        auto& M = s->h64[0];
-        for (int c = 0; c < 3; ++c)
-            TNG_HIP(hipMemcpyAsync(M.b.p + c * ns, b[c], ns * sizeof(double), hipMemcpyDeviceToDevice, st));
-        tng::vcycle<double>(s, 0, M.b.p, s->k64.t.p);
-        for (int c = 0; c < 3; ++c)
-            TNG_HIP(hipMemcpyAsync(x[c], s->k64.t.p + c * ns, ns * sizeof(double), hipMemcpyDeviceToDevice, st));
+        const double* bd[3] = {(const double*)b[0], (const double*)b[1], (const double*)b[2]};
+        double* xd[3] = {(double*)x[0], (double*)x[1], (double*)x[2]};
+        tng::vcycle_fields<double>(s, bd, xd);
     }
     TNG_API_END
 }
