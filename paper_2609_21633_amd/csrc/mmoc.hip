@@ -11,14 +11,20 @@
 // refinement of the 20 icosahedron faces (two per diamond), and the child
 // triangles of a triangle cover exactly its cone (their outer edges lie on
 // the parent's great circles), so the triangle is found by testing the 20
-// faces and then descending one refinement level at a time into the child
-// (of four) with the largest min(a, b, c).  In a diamond's index space a
-// triangle of level size S at origin (i0, j0) is
+// faces (the one whose centroid is nearest in direction: the faces of the regular
+// icosahedron are the Voronoi cells of their centroids) and then descending one refinement
+// level at a time into the child (of four): a corner child when the point lies beyond the
+// plane of that corner's two edge midpoints, else the centre one.  In a diamond's index
+// space a triangle of level size S at origin (i0, j0) is
 //   type 0: (i0, j0), (i0+S, j0), (i0, j0+S);  type 1: (i0+S, j0+S), (i0, j0+S), (i0+S, j0)
 // and the coarse nodes are the fine nodes at multiples of S, so the finest
-// level's unit vectors serve every level.
+// level's unit vectors serve every level.  Bound by FP64 arithmetic and the loads of the
+// descent: three plane signs a level and one division per location, instead of Cramer's
+// rule with its three divisions for all twenty faces and four children a level ((64,64):
+// 790 -> 155 us).
 #include <cmath>
 
+#include "batch_dev.hpp"
 #include "mg.hpp"
 #include "tng_internal.hpp"
 
@@ -41,23 +47,8 @@ __device__ __forceinline__ void cross3(const double* a, const double* b, double*
     c[2] = a[0] * b[1] - a[1] * b[0];
 }
 
-// (a, b, c) of x over the triangle (d, i0, j0, S, w); returns min(a, b, c) / lam, or
-// -inf when the triangle lies on the far side (lam <= 0: all three coefficients can then
-// be negative, and their quotient by lam positive)
-__device__ double bary(const LocGeo& G, const double x[3], int d, int i0, int j0, int S, int w, double abc[3]) {
-    const double* s0 = w == 0 ? unit_at(G, d, i0, j0) : unit_at(G, d, i0 + S, j0 + S);
-    const double* s1 = w == 0 ? unit_at(G, d, i0 + S, j0) : unit_at(G, d, i0, j0 + S);
-    const double* s2 = w == 0 ? unit_at(G, d, i0, j0 + S) : unit_at(G, d, i0 + S, j0);
-    double c12[3], c20[3], c01[3];
-    cross3(s1, s2, c12);
-    cross3(s2, s0, c20);
-    cross3(s0, s1, c01);
-    const double D = s0[0] * c12[0] + s0[1] * c12[1] + s0[2] * c12[2];
-    abc[0] = (x[0] * c12[0] + x[1] * c12[1] + x[2] * c12[2]) / D;
-    abc[1] = (x[0] * c20[0] + x[1] * c20[1] + x[2] * c20[2]) / D;
-    abc[2] = (x[0] * c01[0] + x[1] * c01[1] + x[2] * c01[2]) / D;
-    const double lam = abc[0] + abc[1] + abc[2];
-    return lam > 0.0 ? fmin(fmin(abc[0], abc[1]), abc[2]) / lam : -1e300;
+__device__ __forceinline__ double dot3(const double* a, const double* b) {
+    return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
 struct Loc {
@@ -65,58 +56,71 @@ struct Loc {
     double xi, eta, zeta;
 };
 
-__device__ Loc locate(const LocGeo& G, const double x[3]) {
-    const int m = G.m;
-    // the 20 icosahedron faces: the two triangles of each diamond's single coarsest cell
-    int bd = 0, bw = 0;
-    double best = -1e300, abc[3];
-    for (int d = 0; d < 10; ++d)
-        for (int w = 0; w < 2; ++w) {
-            const double sc = bary(G, x, d, 0, 0, m, w, abc);
-            if (sc > best) {
-                best = sc;
-                bd = d;
-                bw = w;
-            }
+// face[2 d + w]: centroid direction of the icosahedron face of diamond d, triangle w
+__device__ Loc locate(const LocGeo& G, const double (&face)[20][3], const double x[3]) {
+    int best = 0;
+    double bs = -1e300;
+#pragma unroll 4
+    for (int f = 0; f < 20; ++f) {
+        const double sc = dot3(x, face[f]);
+        if (sc > bs) {
+            bs = sc;
+            best = f;
         }
-    int i0 = 0, j0 = 0, w = bw;
-    for (int S = m; S > 1; S >>= 1) {
-        const int h = S >> 1;
-        // children (origin offsets in units of h, type)
-        int ci[4], cj[4], cw[4];
-        if (w == 0) {
-            ci[0] = i0;     cj[0] = j0;     cw[0] = 0;
-            ci[1] = i0 + h; cj[1] = j0;     cw[1] = 0;
-            ci[2] = i0;     cj[2] = j0 + h; cw[2] = 0;
-            ci[3] = i0;     cj[3] = j0;     cw[3] = 1;
-        } else {
-            ci[0] = i0 + h; cj[0] = j0 + h; cw[0] = 1;
-            ci[1] = i0;     cj[1] = j0 + h; cw[1] = 1;
-            ci[2] = i0 + h; cj[2] = j0;     cw[2] = 1;
-            ci[3] = i0 + h; cj[3] = j0 + h; cw[3] = 0;
-        }
-        double bs = -1e300;
-        int bc = 0;
-        for (int c = 0; c < 4; ++c) {
-            const double sc = bary(G, x, bd, ci[c], cj[c], h, cw[c], abc);
-            if (sc > bs) {
-                bs = sc;
-                bc = c;
-            }
-        }
-        i0 = ci[bc];
-        j0 = cj[bc];
-        w = cw[bc];
     }
-    bary(G, x, bd, i0, j0, 1, w, abc);
-    double lam = abc[0] + abc[1] + abc[2];
+    const int d = best >> 1;
+    int i0 = 0, j0 = 0, w = best & 1;
+    for (int S = G.m; S > 1; S >>= 1) {
+        const int h = S >> 1;
+        // edge midpoints opposite to corners 2, 0, 1: m01 on the i edge through the first
+        // corner, m12 on the split diagonal, m20 on the j edge
+        const int o = w == 0 ? 0 : S;
+        const double* p01 = unit_at(G, d, i0 + h, j0 + o);
+        const double* p12 = unit_at(G, d, i0 + h, j0 + h);
+        const double* p20 = unit_at(G, d, i0 + o, j0 + h);
+        const double m01[3] = {p01[0], p01[1], p01[2]}, m12[3] = {p12[0], p12[1], p12[2]},
+                     m20[3] = {p20[0], p20[1], p20[2]};
+        double n0[3], n1[3], n2[3];
+        cross3(m01, m20, n0);
+        cross3(m12, m01, n1);
+        cross3(m20, m12, n2);
+        const double c0 = dot3(x, n0), c1 = dot3(x, n1), c2 = dot3(x, n2);
+        // corners in the triangle's own order: type 0 (i0, j0), (i0+S, j0), (i0, j0+S), type 1
+        // (i0+S, j0+S), (i0, j0+S), (i0+S, j0)
+        const int a = w == 0 ? 0 : h, q = h - a;    // offset of corner 0's child, and of the others'
+        if (c0 > 0.0) {
+            i0 += a;
+            j0 += a;
+        } else if (c1 > 0.0) {
+            i0 += q;
+            j0 += a;
+        } else if (c2 > 0.0) {
+            i0 += a;
+            j0 += q;
+        } else {
+            i0 += a;
+            j0 += a;
+            w ^= 1;
+        }
+    }
+    const double* s0 = w == 0 ? unit_at(G, d, i0, j0) : unit_at(G, d, i0 + 1, j0 + 1);
+    const double* s1 = w == 0 ? unit_at(G, d, i0 + 1, j0) : unit_at(G, d, i0, j0 + 1);
+    const double* s2 = w == 0 ? unit_at(G, d, i0, j0 + 1) : unit_at(G, d, i0 + 1, j0);
+    double c12[3], c20[3], c01[3];
+    cross3(s1, s2, c12);
+    cross3(s2, s0, c20);
+    cross3(s0, s1, c01);
+    const double ca = dot3(x, c12), cb = dot3(x, c20), cc = dot3(x, c01);
+    const double sum = ca + cb + cc;
+    double lam = sum / dot3(s0, c12);
     Loc L;
-    L.d = bd;
+    L.d = d;
     L.ci = i0;
     L.cj = j0;
     L.w = w;
-    L.xi = abc[1] / lam;
-    L.eta = abc[2] / lam;
+    const double inv = 1.0 / sum;
+    L.xi = cb * inv;
+    L.eta = cc * inv;
     // a point outside the shell is brought back radially onto it
     lam = fmin(fmax(lam, G.r_in), G.r_out);
     int k = (int)floor((lam - G.r_in) / G.dr);
@@ -143,27 +147,33 @@ __device__ double interp(const LocGeo& G, const Loc& L, const double* __restrict
     return v;
 }
 
-__global__ void mmoc_departure_kernel(LocGeo G, const double* __restrict__ u0, const double* __restrict__ u1,
-                                      const double* __restrict__ u2, const double* __restrict__ Tn, double dt,
-                                      double* __restrict__ That, long long nslots) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(128) mmoc_departure_kernel(LocGeo G, MagicDiv dn1, const double* __restrict__ u0,
+                                                             const double* __restrict__ u1,
+                                                             const double* __restrict__ u2,
+                                                             const double* __restrict__ Tn, double dt,
+                                                             double* __restrict__ That, unsigned nslots) {
+    __shared__ double face[20][3];
+    if (threadIdx.x < 20) {
+        const int d = threadIdx.x >> 1, w = threadIdx.x & 1, m = G.m;
+        const double* a = w == 0 ? unit_at(G, d, 0, 0) : unit_at(G, d, m, m);
+        const double* b = unit_at(G, d, m, 0);
+        const double* c = unit_at(G, d, 0, m);
+        for (int x = 0; x < 3; ++x) face[threadIdx.x][x] = a[x] + b[x] + c[x];
+    }
+    __syncthreads();
+    const unsigned t = xcd_block() * 128u + threadIdx.x;
     if (t >= nslots) return;
-    const int n = G.n, m = G.m;
-    const int k = (int)(t % (n + 1));
-    long long r = t / (n + 1);
-    const int j = (int)(r % (m + 1));
-    r /= (m + 1);
-    const int i = (int)(r % (m + 1));
-    const int d = (int)(r / (m + 1));
+    const unsigned lat = mdiv(t, dn1);
+    const int k = (int)(t - lat * (unsigned)(G.n + 1));
     const double rk = G.r_in + k * G.dr;
-    const double* s = unit_at(G, d, i, j);
+    const double* s = G.unit + (size_t)lat * 3;
     const double x[3] = {rk * s[0], rk * s[1], rk * s[2]};
     // explicit midpoint rule backwards over dt (eq:departure)
     const double xm[3] = {x[0] - 0.5 * dt * u0[t], x[1] - 0.5 * dt * u1[t], x[2] - 0.5 * dt * u2[t]};
-    const Loc Lm = locate(G, xm);
+    const Loc Lm = locate(G, face, xm);
     const double um[3] = {interp(G, Lm, u0), interp(G, Lm, u1), interp(G, Lm, u2)};
     const double xh[3] = {x[0] - dt * um[0], x[1] - dt * um[1], x[2] - dt * um[2]};
-    That[t] = interp(G, locate(G, xh), Tn);
+    That[t] = interp(G, locate(G, face, xh), Tn);
 }
 
 }  // namespace
@@ -173,8 +183,8 @@ void mmoc_departure(const tng_ctx* ctx, const Level& L, const double* const u[3]
     LocGeo G{L.unit64.p, L.m, L.n, L.r_in, L.r_out, L.dr()};
     const long long ns = L.node_slots();
     ScopedKernelTimer timer(ctx, "mmoc_departure");
-    mmoc_departure_kernel<<<(unsigned)((ns + 127) / 128), 128, 0, ctx->stream>>>(G, u[0], u[1], u[2], Tn, dt, That,
-                                                                                 ns);
+    mmoc_departure_kernel<<<(unsigned)((ns + 127) / 128), 128, 0, ctx->stream>>>(
+        G, magic_div((unsigned)(L.n + 1)), u[0], u[1], u[2], Tn, dt, That, (unsigned)ns);
     TNG_HIP(hipGetLastError());
     // copies of a duplicate node computed the same value up to rounding of their own
     // coordinates: make them equal

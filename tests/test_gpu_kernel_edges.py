@@ -171,3 +171,25 @@ def test_transfers(tng, ctx, dtype, tol, mt, nr):
     got_f = lm.from_lib(ft.double().cpu().numpy(), check_dups=1e-15)
     assert np.linalg.norm(got_c - want_c) <= tol * np.linalg.norm(want_c)
     assert np.linalg.norm(got_f - want_f) <= tol * np.linalg.norm(want_f)
+
+
+# one refinement step and more, points beyond both spheres and several cells away (the flow
+# crosses diamond edges and five-ring vertices)
+@pytest.mark.parametrize("mt,nr,dt", [(2, 3, 2e-3), (8, 5, 5e-3), (16, 7, 2e-3)])
+def test_advection(tng, ctx, mt, nr, dt):
+    """Departure points by descent against the oracle's brute-force location: the interpolant is
+    continuous across wedges, so rounding at an edge stays rounding (1e-12 of max |T| = 1)."""
+    import torch
+    from oracle.mmoc import departure_points, interpolate
+    mesh = tng.Mesh(ctx, mt, nr, levels=1)
+    om = ShellMesh(mt, nr)
+    lm = LayoutMap(*mesh.coords(0), om)
+    rng = np.random.default_rng(8)
+    u = 30.0 * rng.standard_normal((om.n_nodes, 3))
+    T = rng.uniform(0.0, 1.0, om.n_nodes)
+    out = torch.full(mesh.shape(0), float("nan"), dtype=torch.float64, device="cuda")
+    tng.mmoc_advect(ctx, mesh, 0, torch.tensor(lm.to_lib(u), device="cuda").contiguous(), dt,
+                    torch.tensor(lm.to_lib(T), device="cuda"), out)
+    torch.cuda.synchronize()
+    want = interpolate(om, T, departure_points(om, u, dt))
+    assert np.abs(lm.from_lib(out.cpu().numpy(), check_dups=1e-15) - want).max() <= 1e-12
