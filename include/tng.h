@@ -210,7 +210,9 @@ int tng_stokes_apply(tng_ctx* ctx, const tng_mesh* mesh, int level, tng_prec pre
 
 /* Decomposition that tng_stokes_apply uses for these arguments (the kernel
  * layout of Sec. 5 as built here; for tests that target its seams and for
- * measurement).  Launches nothing.  out[0..7] = cell columns per workgroup
+ * measurement).  Small levels take the viscous block alone and the full operator
+ * without options gathered per node instead, unless a band count is forced: the
+ * decomposition is then the one a forced count would use.  Launches nothing.  out[0..7] = cell columns per workgroup
  * tile, waves per column (radial split), cells per lane, waves per workgroup,
  * tiles per diamond, bands per diamond (the per-launch choice, or the forced
  * count of tng_ctx_set_apply_bands), radial ranges per column, cells per

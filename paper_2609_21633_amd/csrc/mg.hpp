@@ -96,6 +96,9 @@ void power_chebyshev(const tng_ctx* ctx, const double* pw, int deg, double lo, d
 template <typename T>
 bool ring_apply_fits(const Level& L);
 template <typename T>
+void ring_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned flags, const void* eta,
+                const void* const u[3], const void* p, void* const yu[3], void* yp);
+template <typename T>
 void ring_cheb_step(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* eta, const double* ab_dev,
                     int k, bool prev_zero, const T* b, const T* invd, const T* xk, T* xo);
 template <typename T>

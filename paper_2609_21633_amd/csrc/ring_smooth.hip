@@ -22,11 +22,12 @@
 #include "batch_dev.hpp"
 #include "mg.hpp"
 #include "tng_internal.hpp"
+#include "wedge.hpp"
 
 namespace tng {
 namespace {
 
-enum { RING_CHEB, RING_RESID, RING_POWER };
+enum { RING_CHEB, RING_RESID, RING_POWER, RING_A, RING_K };
 
 template <typename T>
 struct RingArgs {
@@ -46,16 +47,111 @@ struct RingArgs {
     MagicDiv dn1;
     T r_in, dr;
     int ns_in, ns_out;
+    // operator apply on separate fields (RING_A, RING_K): u and y per component, pressure
+    const T* __restrict__ xs[3];
+    T* ys[3];
+    const T* __restrict__ p;
+    T* yp;
+    int m;
+    unsigned nbu;                 // workgroups of the velocity rows; the pressure rows follow
+    MagicDiv dm, dn1p;            // division by m, nc + 1
+    const int* __restrict__ ring_tri_p;
+    unsigned nsp;
 };
+
+// Iso-W1 weights without the radial ones: corner lc of the coarse quad at q_c of wedge w in
+// the fine cell (a, b) of it.
+template <typename T>
+__device__ __forceinline__ T iso_lat(int a, int b, int w, int lc) {
+    constexpr IsoWeights<T> iso = make_iso_weights<T>();
+    T v = T(0);
+#pragma unroll
+    for (int q = 0; q < 32; ++q)
+        if (q == ((a * 2 + b) * 2 + w) * 4 + lc) v = iso.lw[q >> 4][(q >> 3) & 1][(q >> 2) & 1][q & 3];
+    return v;
+}
+
+// Pressure rows y_p = B u of four coarse nodes: the 96 threads of a node take the six coarse
+// triangles around it, times the four fine triangles in each, times the four fine layers
+// around its layer, one wedge each; summed in a fixed order.
+template <typename T>
+__device__ __forceinline__ void ring_pressure_rows(const RingArgs<T>& a, unsigned blk, T* part) {
+    const int node = threadIdx.x & 3, f = (threadIdx.x >> 2) & 3, q = (threadIdx.x >> 4) & 3, r = threadIdx.x >> 6;
+    const unsigned t = blk * 4u + node, tc = min(t, a.nsp - 1);
+    const int m = a.m, mc = m / 2, nc = a.n / 2;
+    const unsigned lat = mdiv(tc, a.dn1p);
+    const int K = (int)(tc - lat * (unsigned)(nc + 1));
+    const int k = 2 * K - 2 + q;                     // fine layer of cells
+    const int code = a.ring_tri_p[lat * 6 + r];
+    T acc = T(0);
+    if (code >= 0 && k >= 0 && k < a.n) {
+        const int cc = code >> 3, wc = (code >> 2) & 1, l = code & 3;
+        const int J = cc % mc, I = (cc / mc) % mc, d = cc / (mc * mc);
+        // the node's corner of the coarse quad, and its radial weight at the layer
+        const int lc = wc == 0 ? l : 3 - l;
+        const T wr = q == 0 || q == 3 ? T(0.25) : T(0.75);
+        const T rm = a.r_in + (T(k) + T(0.5)) * a.dr, r2 = T(2) * rm;
+        const bool z0 = a.ns_in && k == 0, z1 = a.ns_out && k + 1 == a.n;
+        // fine triangles of the coarse one: at its three corners, and the centre
+        const int ca = wc == 0 ? (f == 1) : (f != 1), cb = wc == 0 ? (f == 2) : (f != 2);
+        const int w = f < 3 ? wc : 1 - wc;
+        const int i = 2 * I + ca, j = 2 * J + cb;
+        const T* g = a.geo + (((size_t)d * m + i) * m + j) * GEO_PER_COL + w * GEO_PER_TRI;
+        const unsigned base = ((unsigned)d * (m + 1) + i) * (m + 1) + j;
+        const unsigned v[3] = {w == 0 ? base : base + m + 2, w == 0 ? base + m + 1 : base + 1,
+                               w == 0 ? base + 1 : base + m + 1};
+        T tr = T(0);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            T b[3], e[3];
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                const T* u = a.xs[c] + ((size_t)v[s] * (a.n + 1) + k);
+                const T ub = u[0], ue = u[1];
+                b[s] = z0 ? T(0) : ub;
+                e[s] = z1 ? T(0) : ue;
+            }
+            tr += ((b[1] - b[0]) + (e[1] - e[0])) * g[c] + ((b[2] - b[0]) + (e[2] - e[0])) * g[3 + c] +
+                  r2 * ((e[0] + e[1] + e[2]) - (b[0] + b[1] + b[2])) * g[6 + c];
+        }
+        acc = -iso_lat<T>(ca, cb, w, lc) * wr * (T(0.5) * rm * g[9]) * tr;
+    }
+    part[threadIdx.x] = acc;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    T v = T(0);
+#pragma unroll
+    for (int x = 0; x < 6; ++x) v += part[64 * x + threadIdx.x];
+#pragma unroll
+    for (int x = 4; x < 64; x <<= 1) v += __shfl_xor(v, x, 64);
+    if (threadIdx.x < 4 && t < a.nsp) a.yp[t] = v;
+}
 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(384) ring_apply_kernel(RingArgs<T> a, SlotBatch sb) {
+    constexpr bool FIELDS = MODE == RING_A || MODE == RING_K;
     __shared__ T part[6][3][64];
     const long long so = slot_off(sb);
+    if constexpr (FIELDS) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            a.xs[c] = at_slot(a.xs[c], so);
+            a.ys[c] = at_slot(a.ys[c], so);
+        }
+        a.p = at_slot(a.p, so);
+        a.yp = at_slot(a.yp, so);
+    }
+    const unsigned blk = xcd_block();
+    if constexpr (MODE == RING_K) {
+        if (blk >= a.nbu) {
+            ring_pressure_rows<T>(a, blk - a.nbu, &part[0][0][0]);
+            return;
+        }
+    }
     const T* eta = at_slot(a.eta, so);
     const T* x = at_slot(a.x, so);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int ti = (int)(xcd_block() * 63u) + lane - 1;      // node slot; lane 0: the one below the first
+    const int ti = (int)(blk * 63u) + lane - 1;      // node slot; lane 0: the one below the first
     const bool mine = lane > 0 && ti < (int)a.ns;
     const unsigned t = (unsigned)min(max(ti, 0), (int)a.ns - 1);
     const int n = a.n, n1 = n + 1;
@@ -66,9 +162,9 @@ __global__ void __launch_bounds__(384) ring_apply_kernel(RingArgs<T> a, SlotBatc
     T bv = T(0), iv = T(0), xv = T(0), pv = T(0), alpha = T(0), beta = T(0);
     const size_t e = (size_t)w * a.ns + t;
     if (w < 3) {
-        if constexpr (MODE != RING_POWER) bv = at_slot(a.b, so)[e];
-        if constexpr (MODE != RING_RESID) iv = at_slot(a.invd, so)[e];
-        xv = x[e];
+        if constexpr (MODE == RING_CHEB || MODE == RING_RESID) bv = at_slot(a.b, so)[e];
+        if constexpr (MODE == RING_CHEB || MODE == RING_POWER) iv = at_slot(a.invd, so)[e];
+        xv = FIELDS ? (w == 0 ? a.xs[0] : (w == 1 ? a.xs[1] : a.xs[2]))[t] : x[e];
         if constexpr (MODE == RING_CHEB) {
             const double* ab = at_slot(a.ab, so);
             alpha = T(ab[2 * a.k]);
@@ -87,15 +183,30 @@ __global__ void __launch_bounds__(384) ring_apply_kernel(RingArgs<T> a, SlotBatc
         for (int s = 0; s < 3; ++s)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const T* xc = x + ((size_t)c * a.ns + v[s] * (unsigned)n1 + k);
+                const T* xc = FIELDS ? a.xs[c] + ((size_t)v[s] * n1 + k) : x + ((size_t)c * a.ns + v[s] * (unsigned)n1 + k);
                 u[0][s][c] = xc[0];
                 u[1][s][c] = xc[1];
             }
         const T ev = T(0.25) * g[9] * eta[((size_t)cell * n + k) * 2 + wd];
+        const T rm = a.r_in + (T(k) + T(0.5)) * a.dr;
+        T vp = T(0);                    // V pbar / (2 r_m) of the wedge
+        if constexpr (MODE == RING_K) {
+            const unsigned row = mdiv((unsigned)cell, a.dm), d = mdiv(row, a.dm);
+            const int j = cell - (int)row * a.m, i = (int)row - (int)d * a.m;
+            const unsigned mc1 = a.m / 2 + 1, nc1 = n / 2 + 1;
+            const T* pc = a.p + ((size_t)((d * mc1 + i / 2) * mc1 + j / 2) * nc1 + k / 2);
+            const T wlo = k & 1 ? T(0.25) : T(0.75), whi = T(1) - wlo;
+#pragma unroll
+            for (int lc = 0; lc < 4; ++lc) {
+                const T* q = pc + (size_t)((lc & 1) * mc1 + (lc >> 1)) * nc1;
+                vp += iso_lat<T>(i & 1, j & 1, wd, lc) * (wlo * q[0] + whi * q[1]);
+            }
+            vp *= T(0.5) * rm * g[9];
+        }
         // velocities on no-slip layers count as zero
         const bool z0 = off0, z1 = a.ns_out && k + 1 == n;
         T a1[3], a2[3], g3[3], L[3][3];
-        const T r2 = T(2) * (a.r_in + (T(k) + T(0.5)) * a.dr);
+        const T r2 = T(2) * rm;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const T g0 = g[c], g1 = g[3 + c], gm = -(g0 + g1);
@@ -116,7 +227,7 @@ __global__ void __launch_bounds__(384) ring_apply_kernel(RingArgs<T> a, SlotBatc
         T S[3][3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            S[c][c] = ev * (L[c][c] + L[c][c] - tr);
+            S[c][c] = ev * (L[c][c] + L[c][c] - tr) - vp;
             const int d = (c + 1) % 3;
             S[c][d] = S[d][c] = ev * (L[c][d] + L[d][c]);
         }
@@ -138,7 +249,9 @@ __global__ void __launch_bounds__(384) ring_apply_kernel(RingArgs<T> a, SlotBatc
     const bool bnd = off0 || offn;
     if (bnd) yv = xv;
     T* out = at_slot(a.out, so);
-    if constexpr (MODE == RING_RESID) {
+    if constexpr (FIELDS) {
+        (w == 0 ? a.ys[0] : (w == 1 ? a.ys[1] : a.ys[2]))[t] = yv;
+    } else if constexpr (MODE == RING_RESID) {
         out[e] = bv - yv;
     } else if constexpr (MODE == RING_POWER) {
         out[e] = iv * yv;
@@ -190,6 +303,37 @@ bool ring_apply_fits(const Level& L) {
     return L.node_slots() <= (sizeof(T) == 8 ? 200000 : 800000);
 }
 
+// y = A_D u or K_D [u; p] in one launch (flags: TNG_OP_A, or with TNG_OP_BT and TNG_OP_B,
+// and TNG_OP_DIRICHLET), instead of the streaming apply's three launches.
+template <typename T>
+void ring_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned flags, const void* eta,
+                const void* const u[3], const void* p, void* const yu[3], void* yp) {
+    const bool ns = (flags & TNG_OP_DIRICHLET) != 0, full = (flags & TNG_OP_B) != 0;
+    RingArgs<T> a = ring_args<T>(L, ns, ns, (const T*)eta, nullptr);
+    for (int c = 0; c < 3; ++c) {
+        a.xs[c] = (const T*)u[c];
+        a.ys[c] = (T*)yu[c];
+    }
+    a.nbu = (unsigned)((L.node_slots() + 62) / 63);
+    unsigned nb = a.nbu;
+    if (full) {
+        a.p = (const T*)p;
+        a.yp = (T*)yp;
+        a.m = L.m;
+        a.dm = magic_div((unsigned)L.m);
+        a.dn1p = magic_div((unsigned)(Lp->n + 1));
+        a.ring_tri_p = Lp->ring_tri.p;
+        a.nsp = (unsigned)Lp->node_slots();
+        nb += (a.nsp + 3) / 4;
+    }
+    const SlotBatch sb = launch_batch();
+    if (full)
+        ring_apply_kernel<T, RING_K><<<dim3(nb, 1, sb.nb), 384, 0, ctx->stream>>>(a, sb);
+    else
+        ring_apply_kernel<T, RING_A><<<dim3(nb, 1, sb.nb), 384, 0, ctx->stream>>>(a, sb);
+    TNG_HIP(hipGetLastError());
+}
+
 template <typename T>
 void ring_cheb_step(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, const T* eta, const double* ab_dev,
                     int k, bool prev_zero, const T* b, const T* invd, const T* xk, T* xo) {
@@ -223,6 +367,8 @@ void ring_power(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, con
 
 #define TNG_RINST(T)                                                                                             \
     template bool ring_apply_fits<T>(const Level&);                                                              \
+    template void ring_apply<T>(const tng_ctx*, const Level&, const Level*, unsigned, const void*,                  \
+                                const void* const[3], const void*, void* const[3], void*);                         \
     template void ring_cheb_step<T>(const tng_ctx*, const Level&, bool, bool, const T*, const double*, int, bool,    \
                                     const T*, const T*, const T*, T*);                                            \
     template void ring_resid<T>(const tng_ctx*, const Level&, bool, bool, const T*, const T*, const T*, T*);          \

@@ -43,6 +43,7 @@
 #include <type_traits>
 
 #include "batch_dev.hpp"
+#include "mg.hpp"
 #include "tng_internal.hpp"
 #include "wedge.hpp"
 
@@ -269,7 +270,6 @@ __global__ void __launch_bounds__(WG * 64) stokes_band_kernel(BandArgs<T> a, Slo
     // the lane holding the workgroup's top node (layer kcend)
     const bool top_lane = (kk[0] <= kcend - 1) && (kcend - 1 <= kk[CPL - 1]);
     const int top_c = kcend - kk[0];
-
     // velocity staging: each radial line of a column over the workgroup's range
     // (KW values of one component) is copied straight from HBM into its ring
     // row, 64 dwords per instruction, lane l moving dword l of each 256-byte
@@ -917,42 +917,43 @@ __global__ void __launch_bounds__(WG * 64) stokes_band_kernel(BandArgs<T> a, Slo
 
 // The passes before the band kernel in one launch: y_p = 0 (np values, when the
 // divergence block is applied), then zeros at the node values that receive two
-// partial sums (node columns on tile seams, node layers on radial-range seams).
+// partial sums (node columns on tile seams, each a contiguous plane of pl values, and node
+// layers on radial-range seams).  A thread writes PRE_PER values 256 apart; 32-bit index
+// arithmetic ((128,128) FP32, 73 MB: 25 -> 12 us against one value and 64-bit divisions per
+// thread).
+constexpr int PRE_PER = 4;
 template <typename T>
-__global__ void pre_apply_kernel(T* yp, long long np, T* y0, T* y1, T* y2, int m, int n, int TI, int KC,
-                                 int nchunk, long long nz, SlotBatch sb) {
-    long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) pre_apply_kernel(T* yp, unsigned np, unsigned bp, T* y0, T* y1, T* y2, int m,
+                                                        int n, int TI, int KC, unsigned nz1, unsigned nz,
+                                                        MagicDiv dpl, MagicDiv dseam, MagicDiv dlat, SlotBatch sb) {
     const long long so = slot_off(sb);
-    if (t < np) {
-        at_slot(yp, so)[t] = T(0);
+    if (blockIdx.x < bp) {
+        const unsigned t0 = blockIdx.x * (256u * PRE_PER) + threadIdx.x;
+        T* y = at_slot(yp, so);
+#pragma unroll
+        for (int e = 0; e < PRE_PER; ++e)
+            if (t0 + 256u * e < np) y[t0 + 256u * e] = T(0);
         return;
     }
-    t -= np;
-    if (t >= nz) return;
-    y0 = at_slot(y0, so);
-    y1 = at_slot(y1, so);
-    y2 = at_slot(y2, so);
-    const int nseam_i = m / TI - 1;
-    const long long n1 = n + 1;
-    const long long ncol = (long long)10 * nseam_i * (m + 1);
-    const long long ldi = (long long)(m + 1) * n1;
-    long long idx;
-    if (t < ncol * n1) {
-        const int k = (int)(t % n1);
-        long long r = t / n1;
-        const int jrow = (int)(r % (m + 1));
-        r /= (m + 1);
-        const int s = (int)(r % nseam_i);
-        const int d = (int)(r / nseam_i);
-        idx = ((long long)d * (m + 1) + (long long)(s + 1) * TI) * ldi + (long long)jrow * n1 + k;
-    } else {
-        t -= ncol * n1;
-        const long long nlat = (long long)10 * (m + 1) * (m + 1);
-        idx = (t % nlat) * n1 + (long long)(t / nlat + 1) * KC;
+    const unsigned t0 = (blockIdx.x - bp) * (256u * PRE_PER) + threadIdx.x;
+    T* const y[3] = {at_slot(y0, so), at_slot(y1, so), at_slot(y2, so)};
+    const unsigned pl = (unsigned)(m + 1) * (unsigned)(n + 1), nseam = (unsigned)(m / TI - 1);
+    const unsigned nlat = 10u * (m + 1) * (m + 1);
+#pragma unroll
+    for (int e = 0; e < PRE_PER; ++e) {
+        const unsigned t = t0 + 256u * e;
+        if (t >= nz) return;
+        unsigned idx;
+        if (t < nz1) {
+            const unsigned q = mdiv(t, dpl), d = mdiv(q, dseam), s = q - d * nseam;
+            idx = (d * (m + 1) + (s + 1) * TI) * pl + (t - q * pl);
+        } else {
+            const unsigned q = t - nz1, c = mdiv(q, dlat);
+            idx = (q - c * nlat) * (n + 1) + (c + 1) * KC;
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) *elem(y[r], idx) = T(0);
     }
-    y0[idx] = T(0);
-    y1[idx] = T(0);
-    y2[idx] = T(0);
 }
 
 // The passes after the band kernel in one launch (disjoint writes, any order):
@@ -960,7 +961,8 @@ __global__ void pre_apply_kernel(T* yp, long long np, T* y0, T* y1, T* y2, int m
 //     of no-slip spheres are left to part 2; on a free-slip sphere the sum is
 //     followed by the boundary row y = P y + N u, P = I - rhat rhat^T, N = rhat rhat^T),
 //  2. the boundary rows of every lateral slot at layers 0 and n: no slip y = u
-//     (viscous block present) or 0; free slip y = P y + N u (N u with the viscous
+//     (viscous block present) or 0 (written by the band kernel instead they cost it more,
+//     346 -> 404 us on (128,128) FP32, than this pass gains, 33 -> 14 us); free slip y = P y + N u (N u with the viscous
 //     block only) at slots outside duplicate groups (part 1 does the others),
 //  3. the interface sum of the pressure copies.
 struct PostArgs {
@@ -1275,13 +1277,14 @@ void band_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned fl
     {
         // y_p = 0 and the seam zeroing, one launch
         const long long np = doB ? Lp->node_slots() : 0;
-        const long long nz = ((doA || doBT) && (a.ntile > 1 || a.nchunk > 1))
-                                 ? 10LL * (a.ntile - 1) * (L.m + 1) * (L.n + 1) +
-                                       10LL * (L.m + 1) * (L.m + 1) * (a.nchunk - 1)
-                                 : 0;
+        const long long nz1 = doA || doBT ? 10LL * (a.ntile - 1) * (L.m + 1) * (L.n + 1) : 0;
+        const long long nz = doA || doBT ? nz1 + 10LL * (L.m + 1) * (L.m + 1) * (a.nchunk - 1) : 0;
         if (np + nz > 0) {
-            pre_apply_kernel<T><<<dim3(nblocks(np + nz, 256), 1, nbz), 256, 0, ctx->stream>>>(
-                a.yp, np, a.y0, a.y1, a.y2, L.m, L.n, a.TI, a.KC, a.nchunk, nz, sb);
+            const unsigned bp = nblocks(np, 256 * PRE_PER);
+            pre_apply_kernel<T><<<dim3(bp + nblocks(nz, 256 * PRE_PER), 1, nbz), 256, 0, ctx->stream>>>(
+                a.yp, (unsigned)np, bp, a.y0, a.y1, a.y2, L.m, L.n, a.TI, a.KC, (unsigned)nz1, (unsigned)nz,
+                magic_div((unsigned)((L.m + 1) * (L.n + 1))), magic_div((unsigned)std::max(1, a.ntile - 1)),
+                magic_div((unsigned)(10 * (L.m + 1) * (L.m + 1))), sb);
             TNG_HIP(hipGetLastError());
         }
     }
@@ -1320,9 +1323,37 @@ void band_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned fl
 
 }  // namespace
 
+// Small levels: the plain viscous block or full operator gathered per node in one launch
+// (ring_smooth.hip), unless a band count is forced.  The pressure rows gather 96 wedges per
+// coarse node, so the full operator takes this form on fewer nodes.  A call as a program
+// makes it (20 us of it in the caller's thread), gathered against streaming: viscous block
+// (8,8) FP32 20 against 23 us, (32,16) FP64 21 against 32, (32,64) FP32, 707,850 slots, 29
+// against 29; full operator (8,8) FP32 21 against 26 us, (16,16), 49,130 slots, FP64 23
+// against 28, but (16,64) FP32, 187,850 slots, 36 against 26 and (16,60) FP64 74 against 28.
+constexpr long long RING_K_SLOTS = 60000;
+template <typename T>
+bool small_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned flags, double hg_alpha, const void* eta,
+                 const void* const u[3], const void* p, void* const yu[3], void* yp) {
+    const unsigned ops = flags & ~(unsigned)TNG_OP_DIRICHLET;
+    if (ctx->apply_bands != 0 || (hg_alpha != 0.0 && (ops & TNG_OP_A)) ||
+        (ops != TNG_OP_A && ops != (TNG_OP_A | TNG_OP_BT | TNG_OP_B)) || !ring_apply_fits<T>(L) ||
+        (ops != TNG_OP_A && L.node_slots() > RING_K_SLOTS))
+        return false;
+    char detail[48] = {0};
+    if (ctx->profile)
+        std::snprintf(detail, sizeof(detail), "%s/%s/%dx%d/ring%s", std::is_same<T, double>::value ? "f64" : "f32",
+                      ops == TNG_OP_A ? "A" : "K", L.m, L.n, launch_batch().nb > 1 ? "/batch" : "");
+    ScopedKernelTimer timer(ctx, "stokes_apply", detail);
+    ring_apply<T>(ctx, L, Lp, flags, eta, u, p, yu, yp);
+    return true;
+}
+
 void launch_stokes_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, tng_prec prec,
                          unsigned flags, double hg_alpha, const void* eta, const void* const u[3], const void* p,
                          void* const yu[3], void* yp) {
+    if (prec == TNG_F64 ? small_apply<double>(ctx, L, Lp, flags, hg_alpha, eta, u, p, yu, yp)
+                        : small_apply<float>(ctx, L, Lp, flags, hg_alpha, eta, u, p, yu, yp))
+        return;
     if (prec == TNG_F64)
         band_apply<double>(ctx, L, Lp, flags, hg_alpha, eta, u, p, yu, yp);
     else

@@ -193,3 +193,63 @@ def test_advection(tng, ctx, mt, nr, dt):
     torch.cuda.synchronize()
     want = interpolate(om, T, departure_points(om, u, dt))
     assert np.abs(lm.from_lib(out.cpu().numpy(), check_dups=1e-15) - want).max() <= 1e-12
+
+
+# full operator and viscous block gathered per node: the smallest shell (five-rings, one
+# coarse cell), 63-node blocks around the columns, remainders of the four coarse nodes a
+# workgroup takes
+@pytest.mark.parametrize("dtype,tol", [("float64", 1e-13), ("float32", 3e-6)])
+@pytest.mark.parametrize("mt,nr", [(2, 2), (4, 30), (4, 34), (2, 258), (8, 62)])
+def test_small_apply(tng, ctx, dtype, tol, mt, nr):
+    """Gathered in one launch against the assembled operator, with Dirichlet rows and without
+    them, element-wise on the row's term magnitudes: sums of at most 72 wedge terms of some
+    50 roundings each (1e-13 in FP64, 3e-6 in FP32)."""
+    import torch
+    dt = getattr(torch, dtype)
+    mesh, om, omp, lm, lmp, eta, orc = shell(tng, ctx, mt, nr)
+    rng = np.random.default_rng(9)
+    u, p = rng.uniform(-1, 1, (om.n_nodes, 3)), rng.uniform(-1, 1, omp.n_nodes)
+    eta_t = torch.tensor(eta[lm.wedge_index()], device="cuda").to(dt)
+    ut = torch.tensor(lm.to_lib(u), device="cuda").to(dt).contiguous()
+    pt = torch.tensor(lmp.to_lib(p), device="cuda").to(dt).contiguous()
+    K = tng.OP_A | tng.OP_BT | tng.OP_B
+    nu = 3 * om.n_nodes
+    for flags, A, BT, B in ((K | tng.OP_DIRICHLET, orc.A_D, orc.BT_D, orc.B_D), (K, orc.A, orc.B.T, orc.B),
+                            (tng.OP_A | tng.OP_DIRICHLET, orc.A_D, None, None), (tng.OP_A, orc.A, None, None)):
+        yu, yp = torch.full_like(ut, float("nan")), torch.full_like(pt, float("nan"))
+        full = BT is not None
+        tng.stokes_apply(ctx, mesh, 0, flags, eta_t, ut, pt if full else None, yu, yp if full else None)
+        torch.cuda.synchronize()
+        M = sp.bmat([[A, BT], [B, None]], format="csr") if full else A
+        x = np.concatenate([u.ravel(), p]) if full else u.ravel()
+        want, scale = M @ x, abs(M) @ np.abs(x)
+        got = lm.from_lib(yu.double().cpu().numpy(), check_dups=1e-15).ravel()
+        if full:
+            got = np.concatenate([got, lmp.from_lib(yp.double().cpu().numpy(), check_dups=tol)])
+        assert len(got) == (nu + omp.n_nodes if full else nu)
+        assert (np.abs(got - want) <= tol * scale).all(), (flags, (np.abs(got - want) / scale).max())
+
+
+# the streaming apply on the shells that the gathered form takes by default: columns of one
+# to several radial stretches and ranges, unequal bands
+@pytest.mark.parametrize("dtype,tol", [("float64", 1e-12), ("float32", 1e-5)])
+@pytest.mark.parametrize("mt,nr,bands", [(4, 96, 1), (4, 160, 2), (4, 320, 1), (8, 62, 3)])
+def test_streaming_apply(tng, ctx, dtype, tol, mt, nr, bands):
+    import torch
+    dt = getattr(torch, dtype)
+    mesh, om, omp, lm, lmp, eta, orc = shell(tng, ctx, mt, nr)
+    rng = np.random.default_rng(10)
+    u, p = rng.uniform(-1, 1, (om.n_nodes, 3)), rng.uniform(-1, 1, omp.n_nodes)
+    ut = torch.tensor(lm.to_lib(u), device="cuda").to(dt).contiguous()
+    pt = torch.tensor(lmp.to_lib(p), device="cuda").to(dt).contiguous()
+    yu, yp = torch.full_like(ut, float("nan")), torch.full_like(pt, float("nan"))
+    ctx.set_apply_bands(bands)
+    try:
+        tng.stokes_apply(ctx, mesh, 0, tng.OP_A | tng.OP_BT | tng.OP_B | tng.OP_DIRICHLET,
+                         torch.tensor(eta[lm.wedge_index()], device="cuda").to(dt), ut, pt, yu, yp)
+        torch.cuda.synchronize()
+    finally:
+        ctx.set_apply_bands(0)
+    ru, rp = orc.apply(u, p)
+    gu, gp = lm.from_lib(yu.double().cpu().numpy()), lmp.from_lib(yp.double().cpu().numpy())
+    assert np.linalg.norm(gu - ru) <= tol * np.linalg.norm(ru) and np.linalg.norm(gp - rp) <= tol * np.linalg.norm(rp)
