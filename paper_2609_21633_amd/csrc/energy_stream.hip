@@ -154,6 +154,7 @@ struct RowV {
 template <typename T, bool FLOW, int TC, int RS>
 __global__ void __launch_bounds__(TC * RS * 64) energy_stream_kernel(EStreamArgs<T> a) {
     constexpr int NW = TC * RS;
+    constexpr bool ROWS = std::is_same<T, double>::value;
     __shared__ T xr[2][NW][64];    // right-column node sums handed to the next column
     __shared__ T rx[2][NW][2];     // top-layer partials of lane 63 (left, right column)
 
@@ -230,15 +231,14 @@ __global__ void __launch_bounds__(TC * RS * 64) energy_stream_kernel(EStreamArgs
         return (rm2 * g[15]) * hq * supg_F(z);
     };
 
-    // one wedge from the temperatures tv[lat][layer] of its six nodes, its mean
-    // velocity ub and V tau (VF); accumulates into out[lat][layer]
+    // one wedge from the temperatures tv[lat][layer] of its six nodes, its
+    // mean velocity ub and V tau (VF); accumulates into out[lat][layer]
     auto wedge = [&](CT* g, const T (&tv)[3][2], const T (&ub)[FLOW ? 3 : 1], T VF, T* (&out)[3]) {
         T A = (tv[1][0] - tv[0][0]) + (tv[1][1] - tv[0][1]);
         T B = (tv[2][0] - tv[0][0]) + (tv[2][1] - tv[0][1]);
         T C = (tv[0][1] + tv[1][1] + tv[2][1]) - (tv[0][0] + tv[1][0] + tv[2][0]);
         if (!cell) A = B = C = T(0);
-        const T V = rm2 * g[15];
-        const T M = V * a.inv_dt * T(1.0 / 6.0);
+        const T M = (rm2 * g[15]) * a.inv_dt * T(1.0 / 6.0);
         T P0 = g[9] * A + g[10] * B + rm * g[12] * C;
         T P1 = g[10] * A + g[11] * B + rm * g[13] * C;
         T P2 = rm * (g[12] * A + g[13] * B) + rm2 * g[14] * C;
@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(TC * RS * 64) energy_stream_kernel(EStreamArgs
             P0 += wt * e0;
             P1 += wt * e1;
             P2 += wt * q2;
-            Q = V * adv * T(1.0 / 6.0);
+            Q = (rm2 * g[15]) * adv * T(1.0 / 6.0);
         }
         const T L0 = -(P0 + P1);
         const T Qb = Q - P2, Qt = Q + P2;
@@ -335,13 +335,21 @@ __global__ void __launch_bounds__(TC * RS * 64) energy_stream_kernel(EStreamArgs
                 }
                 const unsigned row = colA + (unsigned)j * ldj;
                 const bool seamL = c == 0 && i0 > 0;
+                // FP64 writes the rows of the spheres (layers 0 and n) itself, y = T; on a tile
+                // seam the right tile adds it like the other rows (plain stores into the lines
+                // of the atomics there are slow).  (128,128) 566 -> 530 us; FP32 leaves them to
+                // a pass: T kept past the barrier costs it the overlap with the next row's
+                // loads ((256,256) 1.15 -> 1.70 ms; the same for the lumped mass taken once
+                // per node here instead of per wedge, 1.59 ms)
+                const bool bnd = ROWS && (k == 0 || k == n);
+                const T tl = k == 0 ? cur.t[0][0] : cur.t[0][1], tr = k == 0 ? cur.t[1][0] : cur.t[1][1];
                 auto put = [&](unsigned off, T v, bool seam) {
                     if (seam)
                         atomicAdd(ptr_bytes(a.y, off), v);
                     else
                         *ptr_bytes(a.y, off) = v;
                 };
-                if (k <= n) put(row + (unsigned)k * SZ, left, seamL);
+                if (k <= n) put(row + (unsigned)k * SZ, bnd ? tl : left, seamL);
                 // the column's top layer when the last stretch's last lane holds the
                 // last cell (otherwise lane 0 of the stretch above, or the lane above,
                 // holds layer n)
@@ -349,7 +357,7 @@ __global__ void __launch_bounds__(TC * RS * 64) energy_stream_kernel(EStreamArgs
                 if (topn) {
                     T v = top63[0];
                     if (c > 0) v += rx[buf][w - RS][1];
-                    put(row + (unsigned)n * SZ, v, seamL);
+                    put(row + (unsigned)n * SZ, ROWS ? cur.t[0][1] : v, seamL);
                 }
                 if (c == TI - 1) {
                     // the tile's right node column
@@ -357,8 +365,8 @@ __global__ void __launch_bounds__(TC * RS * 64) energy_stream_kernel(EStreamArgs
                     const unsigned rrow = row + ldi;
                     T right = own[1];
                     if (lane == 0 && h > 0) right += rx[buf][w - 1][1];
-                    if (k <= n) put(rrow + (unsigned)k * SZ, right, seamR);
-                    if (topn) put(rrow + (unsigned)n * SZ, top63[1], seamR);
+                    if (k <= n) put(rrow + (unsigned)k * SZ, bnd ? (seamR ? T(0) : tr) : right, seamR);
+                    if (topn) put(rrow + (unsigned)n * SZ, ROWS ? (seamR ? T(0) : cur.t[1][1]) : top63[1], seamR);
                 }
             }
         }
@@ -377,18 +385,16 @@ __global__ void __launch_bounds__(TC * RS * 64) energy_stream_kernel(EStreamArgs
     }
 }
 
-// zero the node columns shared by two tiles (i = multiples of TC inside the diamond)
+// zero the node columns shared by two tiles (i = multiples of TC inside the diamond), each a
+// contiguous plane of pl values: blockIdx.y is the seam, d (nseam) + s
 template <typename T>
-__global__ void zero_tile_seams_kernel(T* y, int m, int n, int TC, long long total) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    const long long colsz = (long long)(m + 1) * (n + 1);
-    const int nseam = (m - 1) / TC;
-    const long long off = t % colsz;
-    const long long r = t / colsz;
-    const int s = (int)(r % nseam) + 1;
-    const int d = (int)(r / nseam);
-    y[((long long)d * (m + 1) + (long long)s * TC) * colsz + off] = T(0);
+__global__ void __launch_bounds__(256) zero_tile_seams_kernel(T* y, int m, unsigned pl, int TC, int nseam) {
+    const int d = blockIdx.y / nseam, s = blockIdx.y % nseam + 1;
+    T* p = y + ((size_t)d * (m + 1) + (size_t)s * TC) * pl;
+    const unsigned t0 = blockIdx.x * 1024u + threadIdx.x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (t0 + 256u * e < pl) p[t0 + 256u * e] = T(0);
 }
 
 // Dirichlet temperature rows of the result: y = T on k = 0 and k = n
@@ -397,6 +403,15 @@ __global__ void copy_layers_kernel(long long ncol, int n, T* y, const T* src) {
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 2 * ncol) return;
     const long long idx = (t >> 1) * (n + 1) + ((t & 1) ? n : 0);
+    y[idx] = src[idx];
+}
+
+// Dirichlet temperature rows of the result: y = T on k = 0 and k = n
+template <typename T>
+__global__ void copy_layers_kernel(unsigned ncol, int n, T* y, const T* src) {
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
+    if (t >= 2 * ncol) return;
+    const size_t idx = (size_t)(t >> 1) * (n + 1) + ((t & 1) ? n : 0);
     y[idx] = src[idx];
 }
 
@@ -412,8 +427,9 @@ void launch_stream(const tng_ctx* ctx, const Level& L, const EStreamArgs<T>& a0)
     a.nband = std::min(nb, L.m);
     const unsigned grid = (unsigned)(10 * a.ntile * a.nband);
     if (L.m > TC) {
-        const long long total = 10LL * ((L.m - 1) / TC) * (L.m + 1) * (L.n + 1);
-        zero_tile_seams_kernel<T><<<nblk(total, 256), 256, 0, ctx->stream>>>(a.y, L.m, L.n, TC, total);
+        const unsigned pl = (unsigned)(L.m + 1) * (unsigned)(L.n + 1);
+        const int nseam = (L.m - 1) / TC;
+        zero_tile_seams_kernel<T><<<dim3(nblk(pl, 1024), 10 * nseam), 256, 0, ctx->stream>>>(a.y, L.m, pl, TC, nseam);
         TNG_HIP(hipGetLastError());
     }
     char detail[48] = {0};
@@ -468,8 +484,12 @@ void energy_apply_stream(const tng_ctx* ctx, const Level& L, const T* const u[3]
             launch_stream<T, false, 4, 4>(ctx, L, a);
     }
     void* f[1] = {y};
+    if (std::is_same<T, double>::value) {
+        launch_interface(ctx, L, prec_of<T>(), 2, 1, f);   // the spheres' rows are complete
+        return;
+    }
     launch_interface(ctx, L, prec_of<T>(), 0, 1, f);
-    copy_layers_kernel<T><<<nblk(2 * L.lat_slots(), 256), 256, 0, ctx->stream>>>(L.lat_slots(), L.n, y, Tin);
+    copy_layers_kernel<T><<<nblk(2 * L.lat_slots(), 256), 256, 0, ctx->stream>>>((unsigned)L.lat_slots(), L.n, y, Tin);
     TNG_HIP(hipGetLastError());
 }
 

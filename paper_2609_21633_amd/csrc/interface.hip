@@ -2,7 +2,8 @@
 // halo exchange, Sec. 2): every node on a diamond edge is stored once per
 // diamond holding it, each copy receives the partial sum of its own diamond's
 // cells, and this pass adds the copies and writes the sum back to all of them,
-// in a fixed order.  (The operator apply does this in its own post-pass.)
+// in a fixed order (mode 0; mode 1 copies the first copy, mode 2 sums all layers but the
+// spheres').  (The operator apply does this in its own post-pass.)
 #include "batch_dev.hpp"
 #include "tng_internal.hpp"
 
@@ -22,12 +23,13 @@ __global__ void interface_kernel(int ngroups, int n1, const int* __restrict__ gp
     if (tid >= (long long)ngroups * n1) return;
     const int gidx = (int)(tid / n1);
     const int k = (int)(tid % n1);
+    if (mode == 2 && (k == 0 || k == n1 - 1)) return;
     const int s0 = gptr[gidx], s1 = gptr[gidx + 1];
     T* fs[4] = {f0, f1, f2, f3};
     for (int c = 0; c < ncomp; ++c) {
         T* f = fs[c];
         T acc = f[(long long)gslot[s0] * n1 + k];
-        if (mode == 0)
+        if (mode != 1)
             for (int s = s0 + 1; s < s1; ++s) acc += f[(long long)gslot[s] * n1 + k];
         for (int s = s0; s < s1; ++s) f[(long long)gslot[s] * n1 + k] = acc;
     }
