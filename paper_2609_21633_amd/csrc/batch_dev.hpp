@@ -50,6 +50,16 @@ __device__ __forceinline__ unsigned xcd_block() {
     return x * q + min(x, r) + (blockIdx.x >> 3);
 }
 
+// Lane l receives lane l + 1's value, lane 63 zero (DPP wavefront shift).
+__device__ __forceinline__ float lane_above(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_above(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x130, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x130, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 // Lane l receives lane l - 1's value, lane 0 zero (DPP wavefront shift).
 __device__ __forceinline__ float lane_below(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));

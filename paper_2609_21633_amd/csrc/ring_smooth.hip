@@ -4,10 +4,11 @@
 //
 // The streaming apply (stokes_apply.hip) walks the cell rows of a band one after another,
 // about ten microseconds on any small level however few cells it has.  Here a workgroup
-// takes 63 consecutive node slots and gives each of their six triangles a wave: a lane
+// takes 62 consecutive node slots and gives each of their six triangles a wave: a lane
 // forms the stress of the wedge above its node in its triangle, and the parts of the two
 // nodes of that wedge in its column: its own (bottom) and the next lane's (top, handed on
-// by a DPP shift; lane 0 only serves lane 1).  The six triangles' parts are added in LDS
+// by a DPP shift; so are the velocities of the layer above, the next lane's, and lanes 0
+// and 63 only serve their neighbours).  The six triangles' parts are added in LDS
 // in ring order, over all diamonds, so that every copy of a node gets the same bits and no
 // interface pass is needed.  A wedge is evaluated for each of its three columns, against
 // once in the streaming apply, so this form is for levels whose launches are bound by
@@ -26,6 +27,13 @@
 
 namespace tng {
 namespace {
+
+// Element idx of a field addressed by a 32-bit byte offset from its base (the levels taken
+// here are small): one register per address instead of two.
+template <typename T>
+__device__ __forceinline__ const T& elem(const T* base, unsigned idx) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + idx * (unsigned)sizeof(T));
+}
 
 enum { RING_CHEB, RING_RESID, RING_POWER, RING_A, RING_K };
 
@@ -151,43 +159,33 @@ __global__ void __launch_bounds__(384) ring_apply_kernel(RingArgs<T> a, SlotBatc
     const T* eta = at_slot(a.eta, so);
     const T* x = at_slot(a.x, so);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int ti = (int)(blk * 63u) + lane - 1;      // node slot; lane 0: the one below the first
-    const bool mine = lane > 0 && ti < (int)a.ns;
+    const int ti = (int)(blk * 62u) + lane - 1;      // node slot; lanes 0 and 63: the ones around
+    const bool mine = lane > 0 && lane < 63 && ti < (int)a.ns;
     const unsigned t = (unsigned)min(max(ti, 0), (int)a.ns - 1);
     const int n = a.n, n1 = n + 1;
     const unsigned lat = mdiv(t, a.dn1);
     const int k = (int)(t - lat * (unsigned)n1);
     const bool off0 = a.ns_in && k == 0, offn = a.ns_out && k == n;
-    // what the closing threads (wave w < 3: component w) need, on its way early
-    T bv = T(0), iv = T(0), xv = T(0), pv = T(0), alpha = T(0), beta = T(0);
-    const size_t e = (size_t)w * a.ns + t;
-    if (w < 3) {
-        if constexpr (MODE == RING_CHEB || MODE == RING_RESID) bv = at_slot(a.b, so)[e];
-        if constexpr (MODE == RING_CHEB || MODE == RING_POWER) iv = at_slot(a.invd, so)[e];
-        xv = FIELDS ? (w == 0 ? a.xs[0] : (w == 1 ? a.xs[1] : a.xs[2]))[t] : x[e];
-        if constexpr (MODE == RING_CHEB) {
-            const double* ab = at_slot(a.ab, so);
-            alpha = T(ab[2 * a.k]);
-            beta = T(ab[2 * a.k + 1]);
-            if (alpha != T(0) && !a.prev_zero) pv = at_slot(a.out, so)[e];
-        }
-    }
     T bot[3] = {T(0), T(0), T(0)}, top[3] = {T(0), T(0), T(0)};
-    const int code = a.ring_tri[lat * 6 + w];
-    if (code >= 0 && k < n && ti >= 0) {
+    // velocities at the triangle's vertices on the node's layer; the next layer's are the next
+    // lane's (every lane of a column has the same vertices)
+    const int code = elem(a.ring_tri, lat * 6 + w);
+    const unsigned v[3] = {lat, (unsigned)elem(a.ring_nb, lat * 6 + w),
+                           (unsigned)elem(a.ring_nb, lat * 6 + (w < 5 ? w + 1 : 0))};
+    T u[2][3][3];   // [layer k, k + 1][vertex][component]
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            u[0][s][c] = FIELDS ? elem(a.xs[c], v[s] * (unsigned)n1 + k) : elem(x, c * a.ns + v[s] * (unsigned)n1 + k);
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) u[1][s][c] = lane_above(u[0][s][c]);
+    if (code >= 0 && k < n && ti >= 0 && lane < 63) {
         const int cell = code >> 3, wd = (code >> 2) & 1, l = code & 3;
-        const unsigned v[3] = {lat, (unsigned)a.ring_nb[lat * 6 + w], (unsigned)a.ring_nb[lat * 6 + (w < 5 ? w + 1 : 0)]};
-        const T* g = a.geo + (size_t)cell * GEO_PER_COL + wd * GEO_PER_TRI;
-        T u[2][3][3];   // [layer k, k + 1][vertex][component]
-#pragma unroll
-        for (int s = 0; s < 3; ++s)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const T* xc = FIELDS ? a.xs[c] + ((size_t)v[s] * n1 + k) : x + ((size_t)c * a.ns + v[s] * (unsigned)n1 + k);
-                u[0][s][c] = xc[0];
-                u[1][s][c] = xc[1];
-            }
-        const T ev = T(0.25) * g[9] * eta[((size_t)cell * n + k) * 2 + wd];
+        const T* g = &elem(a.geo, (unsigned)(cell * GEO_PER_COL + wd * GEO_PER_TRI));
+        const T ev = T(0.25) * g[9] * elem(eta, ((unsigned)cell * (unsigned)n + k) * 2 + wd);
         const T rm = a.r_in + (T(k) + T(0.5)) * a.dr;
         T vp = T(0);                    // V pbar / (2 r_m) of the wedge
         if constexpr (MODE == RING_K) {
@@ -239,6 +237,21 @@ __global__ void __launch_bounds__(384) ring_apply_kernel(RingArgs<T> a, SlotBatc
             top[c] = P + Q;
         }
     }
+    // what the closing threads (wave w < 3: component w) need (loaded here: held over
+    // the stress they cost ten registers and a sixth wave per SIMD, (32,32) FP64 420 -> 388 us)
+    T bv = T(0), iv = T(0), xv = T(0), pv = T(0), alpha = T(0), beta = T(0);
+    const unsigned e = w * a.ns + t;
+    if (w < 3) {
+        if constexpr (MODE == RING_CHEB || MODE == RING_RESID) bv = at_slot(a.b, so)[e];
+        if constexpr (MODE == RING_CHEB || MODE == RING_POWER) iv = at_slot(a.invd, so)[e];
+        xv = FIELDS ? (w == 0 ? a.xs[0] : (w == 1 ? a.xs[1] : a.xs[2]))[t] : x[e];
+        if constexpr (MODE == RING_CHEB) {
+            const double* ab = at_slot(a.ab, so);
+            alpha = T(ab[2 * a.k]);
+            beta = T(ab[2 * a.k + 1]);
+            if (alpha != T(0) && !a.prev_zero) pv = at_slot(a.out, so)[e];
+        }
+    }
 #pragma unroll
     for (int c = 0; c < 3; ++c) part[w][c][lane] = bot[c] + lane_below(top[c]);
     __syncthreads();
@@ -285,7 +298,7 @@ RingArgs<T> ring_args(const Level& L, bool ns_in, bool ns_out, const T* eta, con
 template <typename T, int MODE>
 void ring_launch(const tng_ctx* ctx, const Level& L, const RingArgs<T>& a) {
     const SlotBatch sb = launch_batch();
-    const unsigned nb = (unsigned)((L.node_slots() + 62) / 63);
+    const unsigned nb = (unsigned)((L.node_slots() + 61) / 62);
     ring_apply_kernel<T, MODE><<<dim3(nb, 1, sb.nb), 384, 0, ctx->stream>>>(a, sb);
     TNG_HIP(hipGetLastError());
 }
@@ -293,14 +306,15 @@ void ring_launch(const tng_ctx* ctx, const Level& L, const RingArgs<T>& a) {
 }  // namespace
 
 // Where one gathered launch beats seam zeroing, streaming apply and update.  V-cycle times
-// with the level's seven steps and residual one way or the other: (16,16) FP64 463 -> 231
-// us, FP32 391 -> 185 us for the levels up to 49,130 slots; (32,32), 359,370 slots, FP32
-// 452 -> 356 us but FP64 540 -> 583 us; (64,64), 2.7 M slots, FP32 1006 -> 1355 us.  The
-// gathered form grows with the slots, the streaming one hardly below a million, so the
-// lines lie between the measured sizes.
+// with the levels' seven steps and residual streamed and gathered: (16,16) FP64 463 and 139
+// us, FP32 391 and 130 us (levels up to 49,130 slots); the level of 359,370 slots of a
+// (32,32) cycle FP64 450 and 388 us, FP32 about 350 and 253 us.  At 2.7 M slots ((64,64)) the
+// first gathered form took 43 us a step more than the streaming one in FP32 and 180 us in
+// FP64: the gathered form grows with the slots, the streaming one hardly below a million,
+// so the lines lie between the measured sizes.
 template <typename T>
 bool ring_apply_fits(const Level& L) {
-    return L.node_slots() <= (sizeof(T) == 8 ? 200000 : 800000);
+    return L.node_slots() <= (sizeof(T) == 8 ? 500000 : 800000);
 }
 
 // y = A_D u or K_D [u; p] in one launch (flags: TNG_OP_A, or with TNG_OP_BT and TNG_OP_B,
@@ -314,7 +328,7 @@ void ring_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned fl
         a.xs[c] = (const T*)u[c];
         a.ys[c] = (T*)yu[c];
     }
-    a.nbu = (unsigned)((L.node_slots() + 62) / 63);
+    a.nbu = (unsigned)((L.node_slots() + 61) / 62);
     unsigned nb = a.nbu;
     if (full) {
         a.p = (const T*)p;

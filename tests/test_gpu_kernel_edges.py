@@ -115,7 +115,7 @@ def test_coarse_correction(tng, ctx, mt, nr):
     assert np.linalg.norm(got - want) <= 1e-10 * np.linalg.norm(want)
 
 
-# gathered smoother: the smallest shell, 63-node blocks around the columns (62, 63 and 64
+# gathered smoother: the smallest shell, 62-node blocks around the columns (62, 63 and 64
 # layers) and several blocks; with hourglass control (hg) the streaming apply and its update
 @pytest.mark.parametrize("dtype,tol", [("float64", 1e-12), ("float32", 1e-5)])
 @pytest.mark.parametrize("mt,nr,degree,hg", [(2, 2, 2, 0.0), (4, 61, 2, 0.0), (4, 62, 3, 0.0), (8, 63, 1, 0.0),
@@ -196,7 +196,7 @@ def test_advection(tng, ctx, mt, nr, dt):
 
 
 # full operator and viscous block gathered per node: the smallest shell (five-rings, one
-# coarse cell), 63-node blocks around the columns, remainders of the four coarse nodes a
+# coarse cell), 62-node blocks around the columns, remainders of the four coarse nodes a
 # workgroup takes
 @pytest.mark.parametrize("dtype,tol", [("float64", 1e-13), ("float32", 3e-6)])
 @pytest.mark.parametrize("mt,nr", [(2, 2), (4, 30), (4, 34), (2, 258), (8, 62)])
