@@ -122,10 +122,12 @@ int energy_gmres(const tng_ctx* ctx, const Level& L, EnergyWS& W, const double* 
             vec_mul<double>(ctx, ns, W.invd.p, W.Vi(j), W.Zi(j));
             energy_op(ctx, L, W, u, dt, W.Zi(j), W.w.p);
             vec_mdot<double>(ctx, W.ds, ns, L.n + 1, nlat, L.owner.p, W.w.p, W.vptr.p, j + 1, dsc, false);
-            vec_maxpy<double>(ctx, ns, dsc, -1.0, W.vptr.p, j + 1, W.w.p);
-            vec_mdot<double>(ctx, W.ds, ns, L.n + 1, nlat, L.owner.p, W.w.p, W.vptr.p, j + 1, dsc + MAX_MDOT, false);
-            vec_maxpy<double>(ctx, ns, dsc + MAX_MDOT, -1.0, W.vptr.p, j + 1, W.w.p);
-            dot1(W.w.p, W.wptr.p + 1, dsc + 2 * MAX_MDOT);
+            // classical Gram-Schmidt, twice, the second dots and the norm in the passes that
+            // update w (three passes over the basis instead of four and one over w)
+            vec_maxpy_mdot<double>(ctx, W.ds, ns, L.n + 1, L.owner.p, dsc, -1.0, W.vptr.p, j + 1, W.w.p,
+                                   dsc + MAX_MDOT, false);
+            vec_maxpy_mdot<double>(ctx, W.ds, ns, L.n + 1, L.owner.p, dsc + MAX_MDOT, -1.0, W.vptr.p, j + 1, W.w.p,
+                                   dsc + 2 * MAX_MDOT, true);
             vec_scale_rsqrt<double>(ctx, ns, dsc + 2 * MAX_MDOT, W.w.p, W.Vi(j + 1));
             TNG_HIP(hipMemcpyAsync(W.host, dsc, (2 * MAX_MDOT + 1) * sizeof(double), hipMemcpyDeviceToHost,
                                    ctx->stream));

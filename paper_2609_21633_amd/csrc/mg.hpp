@@ -144,6 +144,11 @@ template <typename T>
 void vec_maxpy_smdot(const tng_ctx* ctx, DotScratch& ds, const Level& Lu, const Level& Lp, const double* coef_dev,
                      double sign, const T* const* vs_dev, int nq, T* y, double* out_dev, bool norm,
                      bool vs_aligned = false);
+// the same over a node field of n slots (n1 layers per column)
+template <typename T>
+void vec_maxpy_mdot(const tng_ctx* ctx, DotScratch& ds, long long n, int n1, const uint8_t* owner,
+                    const double* coef_dev, double sign, const T* const* vs_dev, int nq, T* y, double* out_dev,
+                    bool norm);
 template <typename T>
 void vec_rand(const tng_ctx* ctx, long long n, unsigned long long seed, T* a);
 template <typename T>

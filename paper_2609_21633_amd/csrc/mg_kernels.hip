@@ -1822,6 +1822,31 @@ void vec_maxpy_smdot(const tng_ctx* ctx, DotScratch& ds, const Level& Lu, const 
     TNG_HIP(hipGetLastError());
 }
 
+// a node field is a Stokes vector without velocity slots
+template <typename T>
+void vec_maxpy_mdot(const tng_ctx* ctx, DotScratch& ds, long long n, int n1, const uint8_t* owner,
+                    const double* coef_dev, double sign, const T* const* vs_dev, int nq, T* y, double* out_dev,
+                    bool norm) {
+    TNG_REQUIRE(nq >= 1 && nq <= MAX_MDOT, "too many vectors in a multi-axpy");
+    TNG_REQUIRE(n < (1LL << 32), "vector length out of range");
+    require_unbatched("vec_maxpy_mdot");
+    const SlotBatch sb;
+    const MagicDiv dn1 = magic_div((unsigned)n1);
+    const int nb = (int)std::min<long long>(DOT_BLOCKS, (n + DOT_BS - 1) / DOT_BS);
+    if (norm) {
+        TNG_NQ_DISPATCH(count_class(sb, nq), (maxpy_dot_kernel<T, NQ, true><<<nb, DOT_BS, 0, ctx->stream>>>(
+                                0u, dn1, 0u, owner, (unsigned)n, dn1, owner, coef_dev, sign, vs_dev, nq, y,
+                                ds.part.p, sb)));
+    } else {
+        TNG_NQ_DISPATCH(count_class(sb, nq), (maxpy_dot_kernel<T, NQ, false><<<nb, DOT_BS, 0, ctx->stream>>>(
+                                0u, dn1, 0u, owner, (unsigned)n, dn1, owner, coef_dev, sign, vs_dev, nq, y,
+                                ds.part.p, sb)));
+    }
+    TNG_HIP(hipGetLastError());
+    mdot_final_kernel<<<norm ? 1 : nq, 256, 0, ctx->stream>>>(nb, norm ? 1 : nq, ds.part.p, out_dev, 0, sb);
+    TNG_HIP(hipGetLastError());
+}
+
 template <typename T>
 void vec_rand(const tng_ctx* ctx, long long n, unsigned long long seed, T* a) {
     require_unbatched("vec_rand");
@@ -1977,6 +2002,8 @@ void vec_schur(const tng_ctx* ctx, long long n, const T* r, const T* mdiag, T* z
                                const T* const*, int, double*, bool, bool);                                 \
     template void vec_maxpy_smdot<T>(const tng_ctx*, DotScratch&, const Level&, const Level&, const double*,  \
                                      double, const T* const*, int, T*, double*, bool, bool);                 \
+    template void vec_maxpy_mdot<T>(const tng_ctx*, DotScratch&, long long, int, const uint8_t*, const double*, double, \
+                                    const T* const*, int, T*, double*, bool);                                 \
     template void vec_rand<T>(const tng_ctx*, long long, unsigned long long, T*);                         \
     template void vec_scale_rsqrt<T>(const tng_ctx*, long long, const double*, const T*, T*);             \
     template void vec_tab_copy<T>(const tng_ctx*, long long, const T*, const T* const*, T*, T* const*, int, \
