@@ -91,10 +91,10 @@ void vec_mul_post(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, c
 // sqrt(pw[1] / pw[0]) from the squared norms of the last two power iterates
 void power_chebyshev(const tng_ctx* ctx, const double* pw, int deg, double lo, double hi, double* ab);
 // The same three uses of A_D x as one launch each (ring_smooth.hip), without hourglass
-// control and on levels where ring_apply_fits: a Chebyshev step, a residual, and a step of
+// control and where ring_apply_fits (small levels, no forced band count): a Chebyshev step, a residual, and a step of
 // the power iteration z = D^-1 A_D x.
 template <typename T>
-bool ring_apply_fits(const Level& L);
+bool ring_apply_fits(const tng_ctx* ctx, const Level& L);
 template <typename T>
 void ring_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned flags, const void* eta,
                 const void* const u[3], const void* p, void* const yu[3], void* yp);

@@ -312,9 +312,10 @@ void ring_launch(const tng_ctx* ctx, const Level& L, const RingArgs<T>& a) {
 // first gathered form took 43 us a step more than the streaming one in FP32 and 180 us in
 // FP64: the gathered form grows with the slots, the streaming one hardly below a million,
 // so the lines lie between the measured sizes.
+// A forced band count asks for the streaming form on every level.
 template <typename T>
-bool ring_apply_fits(const Level& L) {
-    return L.node_slots() <= (sizeof(T) == 8 ? 500000 : 800000);
+bool ring_apply_fits(const tng_ctx* ctx, const Level& L) {
+    return ctx->apply_bands == 0 && L.node_slots() <= (sizeof(T) == 8 ? 500000 : 800000);
 }
 
 // y = A_D u or K_D [u; p] in one launch (flags: TNG_OP_A, or with TNG_OP_BT and TNG_OP_B,
@@ -380,7 +381,7 @@ void ring_power(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, con
 }
 
 #define TNG_RINST(T)                                                                                             \
-    template bool ring_apply_fits<T>(const Level&);                                                              \
+    template bool ring_apply_fits<T>(const tng_ctx*, const Level&);                                              \
     template void ring_apply<T>(const tng_ctx*, const Level&, const Level*, unsigned, const void*,                  \
                                 const void* const[3], const void*, void* const[3], void*);                         \
     template void ring_cheb_step<T>(const tng_ctx*, const Level&, bool, bool, const T*, const double*, int, bool,    \

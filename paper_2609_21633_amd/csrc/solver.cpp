@@ -254,7 +254,7 @@ void chebyshev_steps(const tng_ctx* ctx, const Level& L, const T* eta, double hg
         void* yu[3] = {yout, yout + ns, yout + 2 * ns};
         launch_stokes_apply_raw(ctx, L, prec_of<T>(), aflags, hg_alpha, eta, u, yu);
     };
-    const bool ring = !twopt && hg_alpha == 0.0 && ring_apply_fits<T>(L);   // small levels: one launch per step
+    const bool ring = !twopt && hg_alpha == 0.0 && ring_apply_fits<T>(ctx, L);   // small levels: one launch per step
     for (int st = 0; st < steps; ++st) {
         for (int k = 0; k < deg; ++k) {
             const bool first = x_zero && st == 0 && k == 0;
@@ -328,7 +328,7 @@ void vcycle(tng_solver* s, int l, const T* b, T* x) {
         apply_A<T>(s, l, M.eta.p, x, M.y.p);
         vec_cast<T, T>(s->ctx, 3 * ns, b, M.r.p);
         vec_axpby<T>(s->ctx, 3 * ns, -1.0, M.y.p, 1.0, M.r.p);
-    } else if (!twopt_flag(s) && s->opts.hg_alpha == 0.0 && ring_apply_fits<T>(*M.L)) {
+    } else if (!twopt_flag(s) && s->opts.hg_alpha == 0.0 && ring_apply_fits<T>(s->ctx, *M.L)) {
         ring_resid<T>(s->ctx, *M.L, true, true, M.eta.p, b, x, M.r.p);
     } else {
         const Level& L = *M.L;
@@ -629,7 +629,7 @@ void power_cheb(tng_solver* s, int l) {
     T* xv[3] = {M.x.p, M.x.p + ns, M.x.p + 2 * ns};
     vec_fs_project<T>(s->ctx, L, fs_bits(s), xv, nullptr);
     double* pw = s->pw.p + 2 * l;
-    const bool ring = !fs_flag(s) && !twopt_flag(s) && s->opts.hg_alpha == 0.0 && ring_apply_fits<T>(L);
+    const bool ring = !fs_flag(s) && !twopt_flag(s) && s->opts.hg_alpha == 0.0 && ring_apply_fits<T>(s->ctx, L);
     int cur = 0;                                     // the iterate: M.x (0) or M.d (1), also in M.xd
     auto norm2 = [&](int which, double* out) {
         vel_dot<T>(s, l, which ? M.d.p : M.x.p, M.xd.p + which, out);

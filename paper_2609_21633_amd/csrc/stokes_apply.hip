@@ -1335,8 +1335,8 @@ template <typename T>
 bool small_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned flags, double hg_alpha, const void* eta,
                  const void* const u[3], const void* p, void* const yu[3], void* yp) {
     const unsigned ops = flags & ~(unsigned)TNG_OP_DIRICHLET;
-    if (ctx->apply_bands != 0 || (hg_alpha != 0.0 && (ops & TNG_OP_A)) ||
-        (ops != TNG_OP_A && ops != (TNG_OP_A | TNG_OP_BT | TNG_OP_B)) || !ring_apply_fits<T>(L) ||
+    if ((hg_alpha != 0.0 && (ops & TNG_OP_A)) ||
+        (ops != TNG_OP_A && ops != (TNG_OP_A | TNG_OP_BT | TNG_OP_B)) || !ring_apply_fits<T>(ctx, L) ||
         (ops != TNG_OP_A && L.node_slots() > RING_K_SLOTS))
         return false;
     char detail[48] = {0};
