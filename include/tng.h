@@ -135,8 +135,10 @@ int tng_ctx_set_apply_bands(tng_ctx* ctx, int bands);
  * context stream around its main kernel, under the name
  * "<kernel>/<precision>/<variant>/<m>x<n>" (kernels "stokes_apply" with
  * variant A, BT, B, A+BT, ... and a "+HG" suffix for hourglass control, then
- * "/b<bands>" and, for serving batches, "/batch"; "energy_apply").  tng_ctx_kernel_stats synchronises on the recorded events
- * and returns the summed elapsed milliseconds and the number of launches
+ * "/b<bands>", or "/ring" on small levels whose nodes gather (the smoother's
+ * update, the residual and the power iteration's scaling are then part of that
+ * kernel), and, for serving batches, "/batch"; "energy_apply").
+ * tng_ctx_kernel_stats synchronises on the recorded events and returns the summed elapsed milliseconds and the number of launches
  * since profiling was (re)enabled, over the names equal to `name` or starting
  * with `name` + "/" (so "stokes_apply" sums every variant); none gives 0 and
  * 0.  tng_ctx_kernel_stats_at returns the index-th recorded full name (copied

@@ -20,6 +20,9 @@
 //   2 r_m grad u = L = E1 a_1 + E2 a_2 + 2 r_m C g3,  2 r_m grad phi_0 = a_0 +- 2 r_m g3,
 // and V / (2 r_m)^2 = g9 / 4: the wedge's part of row 0 is
 //   eta g9/4 (L + L^T - 2/3 tr L) (a_0 +- 2 r_m g3), with no division (+ at its top node).
+#include <cstdio>
+#include <type_traits>
+
 #include "batch_dev.hpp"
 #include "mg.hpp"
 #include "tng_internal.hpp"
@@ -295,10 +298,18 @@ RingArgs<T> ring_args(const Level& L, bool ns_in, bool ns_out, const T* eta, con
     return a;
 }
 
+// workgroups of the velocity rows
+unsigned ring_blocks(const Level& L) { return (unsigned)((L.node_slots() + 61) / 62); }
+
+// nb workgroups, timed like the streaming apply (what is fused with the operator included)
 template <typename T, int MODE>
-void ring_launch(const tng_ctx* ctx, const Level& L, const RingArgs<T>& a) {
+void ring_launch(const tng_ctx* ctx, const Level& L, const RingArgs<T>& a, unsigned nb) {
     const SlotBatch sb = launch_batch();
-    const unsigned nb = (unsigned)((L.node_slots() + 61) / 62);
+    char detail[48] = {0};
+    if (ctx->profile)
+        std::snprintf(detail, sizeof(detail), "%s/%s/%dx%d/ring%s", std::is_same<T, double>::value ? "f64" : "f32",
+                      MODE == RING_K ? "K" : "A", L.m, L.n, sb.nb > 1 ? "/batch" : "");
+    ScopedKernelTimer timer(ctx, "stokes_apply", detail);
     ring_apply_kernel<T, MODE><<<dim3(nb, 1, sb.nb), 384, 0, ctx->stream>>>(a, sb);
     TNG_HIP(hipGetLastError());
 }
@@ -329,8 +340,7 @@ void ring_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned fl
         a.xs[c] = (const T*)u[c];
         a.ys[c] = (T*)yu[c];
     }
-    a.nbu = (unsigned)((L.node_slots() + 61) / 62);
-    unsigned nb = a.nbu;
+    a.nbu = ring_blocks(L);
     if (full) {
         a.p = (const T*)p;
         a.yp = (T*)yp;
@@ -339,14 +349,10 @@ void ring_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned fl
         a.dn1p = magic_div((unsigned)(Lp->n + 1));
         a.ring_tri_p = Lp->ring_tri.p;
         a.nsp = (unsigned)Lp->node_slots();
-        nb += (a.nsp + 3) / 4;
+        ring_launch<T, RING_K>(ctx, L, a, a.nbu + (a.nsp + 3) / 4);
+    } else {
+        ring_launch<T, RING_A>(ctx, L, a, a.nbu);
     }
-    const SlotBatch sb = launch_batch();
-    if (full)
-        ring_apply_kernel<T, RING_K><<<dim3(nb, 1, sb.nb), 384, 0, ctx->stream>>>(a, sb);
-    else
-        ring_apply_kernel<T, RING_A><<<dim3(nb, 1, sb.nb), 384, 0, ctx->stream>>>(a, sb);
-    TNG_HIP(hipGetLastError());
 }
 
 template <typename T>
@@ -359,7 +365,7 @@ void ring_cheb_step(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out,
     a.ab = ab_dev;
     a.k = k;
     a.prev_zero = prev_zero ? 1 : 0;
-    ring_launch<T, RING_CHEB>(ctx, L, a);
+    ring_launch<T, RING_CHEB>(ctx, L, a, ring_blocks(L));
 }
 
 template <typename T>
@@ -368,7 +374,7 @@ void ring_resid(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, con
     RingArgs<T> a = ring_args<T>(L, ns_in, ns_out, eta, x);
     a.b = b;
     a.out = r;
-    ring_launch<T, RING_RESID>(ctx, L, a);
+    ring_launch<T, RING_RESID>(ctx, L, a, ring_blocks(L));
 }
 
 template <typename T>
@@ -377,7 +383,7 @@ void ring_power(const tng_ctx* ctx, const Level& L, bool ns_in, bool ns_out, con
     RingArgs<T> a = ring_args<T>(L, ns_in, ns_out, eta, x);
     a.invd = invd;
     a.out = z;
-    ring_launch<T, RING_POWER>(ctx, L, a);
+    ring_launch<T, RING_POWER>(ctx, L, a, ring_blocks(L));
 }
 
 #define TNG_RINST(T)                                                                                             \

@@ -1339,11 +1339,6 @@ bool small_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned f
         (ops != TNG_OP_A && ops != (TNG_OP_A | TNG_OP_BT | TNG_OP_B)) || !ring_apply_fits<T>(ctx, L) ||
         (ops != TNG_OP_A && L.node_slots() > RING_K_SLOTS))
         return false;
-    char detail[48] = {0};
-    if (ctx->profile)
-        std::snprintf(detail, sizeof(detail), "%s/%s/%dx%d/ring%s", std::is_same<T, double>::value ? "f64" : "f32",
-                      ops == TNG_OP_A ? "A" : "K", L.m, L.n, launch_batch().nb > 1 ? "/batch" : "");
-    ScopedKernelTimer timer(ctx, "stokes_apply", detail);
     ring_apply<T>(ctx, L, Lp, flags, eta, u, p, yu, yp);
     return true;
 }

@@ -123,3 +123,31 @@ def test_forced_bands_stream_the_solve(tng, profiled, mixed):
     seen = applies(profiled)
     assert all("/ring" not in k for k in seen) and {"A/8x8/b2", "A/4x4/b2", "K/8x8/b2"} <= set(seen), seen
     s.close()
+
+
+# levels that gather: the smoother, its residual and the power iteration are timed like the
+# applies of the streaming form
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_gathered_smoother_is_timed(tng, profiled, dtype):
+    import torch
+    mesh, om, lm, A, eta_t, d, bx, lib = smoother_case(tng, profiled, 4, 6, getattr(torch, dtype))
+    tng.smooth(profiled, mesh, 0, eta_t, d, lib[0], lib[1], 2, 3, 0.3, 3.3)
+    assert applies(profiled) == {"A/4x6/ring": 6}
+    ms, n = profiled.kernel_stats("stokes_apply")
+    assert n == 6 and ms > 0.0
+
+
+def test_gathered_solver_applies_are_timed(tng, profiled):
+    """Set-up: power_its applies on each smoothed level; a V-cycle from zero: per level one apply
+    less than degree times steps before the coarse correction, the residual, and degree times
+    steps after it."""
+    import torch
+    mesh = shell(tng, profiled, 8, 8, levels=3)[0]
+    s = tng.StokesSolver(profiled, mesh, mixed=0, pre=1, post=2, cheb_degree=2, power_its=5)
+    s.setup(torch.ones(mesh.wedge_shape(0), dtype=torch.float64, device="cuda"))
+    assert applies(profiled) == {"A/8x8/ring": 5, "A/4x4/ring": 5}
+    profiled.profile(True)
+    b = torch.ones((3,) + mesh.shape(0), dtype=torch.float64, device="cuda")
+    s.vcycle(b, torch.empty_like(b))
+    assert applies(profiled) == {"A/8x8/ring": 6, "A/4x4/ring": 6}
+    s.close()
