@@ -294,31 +294,61 @@ __global__ void __launch_bounds__(256) pmass_kernel(const T* __restrict__ eta, c
 // coarse node copies it, one on a coarse edge takes the mean of the edge's
 // end nodes (edges along i, along j, or the split diagonal), radially odd
 // layers take the mean of the two coarse layers.  y += P x (add) or y = P x.
+struct ProlongNode {
+    size_t a, b;      // the ends of the coarse edge that a fine node lies on (the same at a coarse node)
+    unsigned edge;    // they differ
+    unsigned up;      // 1: on an odd layer, between coarse layers
+};
+__device__ __forceinline__ ProlongNode prolong_node(unsigned t, int mf, int nf, MagicDiv dn1, MagicDiv dm1) {
+    const unsigned mf1 = mf + 1, nc1 = nf / 2 + 1, mc1 = mf / 2 + 1;
+    const unsigned lat = mdiv(t, dn1), k = t - lat * (nf + 1);
+    const unsigned row = mdiv(lat, dm1), j = lat - row * mf1;
+    const unsigned d = mdiv(row, dm1), i = row - d * mf1;
+    const unsigned oi = i & 1, oj = j & 1;
+    const unsigned a = (d * mc1 + i / 2) * mc1 + j / 2 + (oi & oj);
+    const unsigned b = a + (oi ? mc1 : 0u) + (oi & oj ? 0u - 1u : oj);
+    return {(size_t)a * nc1 + k / 2, (size_t)b * nc1 + k / 2, oi | oj, k & 1};
+}
+
+// y += P x, a component per thread
 template <typename T>
-__global__ void __launch_bounds__(256) prolong_kernel(int mf, int nf, const T* __restrict__ c0,
-                                                      const T* __restrict__ c1, const T* __restrict__ c2, T* f0, T* f1,
-                                                      T* f2, int add, unsigned nslots, MagicDiv dn1, MagicDiv dm1,
-                                                      SlotBatch sb) {
+__global__ void __launch_bounds__(256) prolong_add_kernel(int mf, int nf, const T* __restrict__ c0,
+                                                          const T* __restrict__ c1, const T* __restrict__ c2, T* f0,
+                                                          T* f1, T* f2, unsigned nslots, MagicDiv dn1, MagicDiv dm1,
+                                                          SlotBatch sb) {
     const long long so = slot_off(sb);
     const unsigned t = blockIdx.x * 256u + threadIdx.x;
     if (t >= nslots) return;
     const T* c = at_slot(blockIdx.y == 0 ? c0 : (blockIdx.y == 1 ? c1 : c2), so);
     T* f = at_slot(blockIdx.y == 0 ? f0 : (blockIdx.y == 1 ? f1 : f2), so);
-    const T old = add ? f[t] : T(0);
-    const unsigned mf1 = mf + 1, nc1 = nf / 2 + 1, mc1 = mf / 2 + 1;
-    const unsigned lat = mdiv(t, dn1), k = t - lat * (nf + 1);
-    const unsigned row = mdiv(lat, dm1), j = lat - row * mf1;
-    const unsigned d = mdiv(row, dm1), i = row - d * mf1;
-    // the ends of the coarse edge the node lies on (the same node twice at a coarse node),
-    // and of the radial interval
-    const unsigned oi = i & 1, oj = j & 1;
-    const unsigned a = (d * mc1 + i / 2) * mc1 + j / 2 + (oi & oj);
-    const unsigned b = a + (oi ? mc1 : 0u) + (oi & oj ? 0u - 1u : oj);
-    const unsigned ok = k & 1, ka = k / 2;
-    const T* ca = c + (size_t)a * nc1 + ka;
-    const T* cb = c + (size_t)b * nc1 + ka;
-    const T v = T(0.25) * ((ca[0] + cb[0]) + (ca[ok] + cb[ok]));
-    f[t] = add ? old + v : v;
+    const T old = f[t];
+    const ProlongNode q = prolong_node(t, mf, nf, dn1, dm1);
+    f[t] = old + T(0.25) * ((c[q.a] + c[q.b]) + (c[q.a + q.up] + c[q.b + q.up]));
+}
+
+// y = P x: a coarse node is copied, whatever its value.  All components per thread:
+// (128,128) FP32 117 -> 84 us, FP64 275 -> 264 us against a component per thread.
+template <typename T>
+__global__ void __launch_bounds__(256) prolong_kernel(int mf, int nf, const T* __restrict__ c0,
+                                                      const T* __restrict__ c1, const T* __restrict__ c2, T* f0, T* f1,
+                                                      T* f2, unsigned nslots, MagicDiv dn1, MagicDiv dm1,
+                                                      SlotBatch sb) {
+    const long long so = slot_off(sb);
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
+    if (t >= nslots) return;
+    const T* const c[3] = {at_slot(c0, so), at_slot(c1, so), at_slot(c2, so)};
+    T* const f[3] = {at_slot(f0, so), at_slot(f1, so), at_slot(f2, so)};
+    const ProlongNode q = prolong_node(t, mf, nf, dn1, dm1);
+    const T w = (q.edge ? T(0.5) : T(1)) * (q.up ? T(0.5) : T(1));
+    T v[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+        const T a0 = c[x][q.a], a1 = c[x][q.a + q.up], b0 = c[x][q.b], b1 = c[x][q.b + q.up];
+        const T s0 = q.edge ? a0 + b0 : a0, s1 = q.edge ? a1 + b1 : a1;
+        v[x] = (q.up ? s0 + s1 : s0) * w;
+    }
+#pragma unroll
+    for (int x = 0; x < 3; ++x) f[x][t] = v[x];
 }
 
 // Restriction R = P^T: a coarse node gathers the fine nodes that interpolate from it, the
@@ -1553,8 +1583,9 @@ template <typename T>
 void mg_prolong(const tng_ctx* ctx, const Level& Lf, const T* const c[3], T* const f[3], bool add) {
     const long long ns = Lf.node_slots();
     const SlotBatch sb = launch_batch();
-    prolong_kernel<T><<<dim3(nblk(ns, 256), 3, sb.nb), 256, 0, ctx->stream>>>(
-        Lf.m, Lf.n, c[0], c[1], c[2], f[0], f[1], f[2], add ? 1 : 0, (unsigned)ns, magic_div((unsigned)(Lf.n + 1)),
+    auto* kernel = add ? prolong_add_kernel<T> : prolong_kernel<T>;
+    kernel<<<dim3(nblk(ns, 256), add ? 3 : 1, sb.nb), 256, 0, ctx->stream>>>(
+        Lf.m, Lf.n, c[0], c[1], c[2], f[0], f[1], f[2], (unsigned)ns, magic_div((unsigned)(Lf.n + 1)),
         magic_div((unsigned)(Lf.m + 1)), sb);
     TNG_HIP(hipGetLastError());
 }

@@ -1,0 +1,80 @@
+"""Infinities and the largest finite values in the field kernels: they reach the nodes whose
+sums hold them, as the sums of the definitions do, and no others."""
+import numpy as np
+import pytest
+
+from oracle.mesh import ShellMesh
+from tests._support import LayoutMap
+
+pytestmark = pytest.mark.gpu
+
+SHELLS = [(4, 6), (8, 62)]
+
+
+@pytest.fixture(scope="module")
+def tng():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_21633_amd as t
+    return t
+
+
+@pytest.fixture(scope="module")
+def ctx(tng):
+    return tng.Context(0)
+
+
+_cache = {}
+
+
+def shell(tng, ctx, mt, nr):
+    """(mesh, oracle mesh, layout map, unique lateral ids of both levels)."""
+    if (mt, nr) not in _cache:
+        mesh = tng.Mesh(ctx, mt, nr, levels=2)
+        om = ShellMesh(mt, nr)
+        _cache[(mt, nr)] = (mesh, om, LayoutMap(*mesh.coords(0), om),
+                            [np.asarray(mesh.unique_ids(l)).ravel() for l in range(2)])
+    return _cache[(mt, nr)]
+
+
+def to_fine(c):
+    """W1 interpolation of node fields [..., 10, m+1, m+1, n+1] to the next finer level, in FP64."""
+    for ax in (-3, -2, -1):
+        s = list(c.shape)
+        s[ax] = 2 * s[ax] - 1
+        f = np.empty(s)
+        ix = lambda sl: tuple([Ellipsis] + [sl if a == ax else slice(None) for a in (-3, -2, -1)])
+        lo, hi = c[ix(slice(None, -1))], c[ix(slice(1, None))]
+        f[ix(slice(None, None, 2))] = c
+        f[ix(slice(1, None, 2))] = 0.5 * lo + 0.5 * hi
+        if ax == -2:
+            # the centre of a coarse quad is the midpoint of its split diagonal
+            odd = f[..., 1::2, 1::2, :]
+            odd[:] = 0.5 * c0[..., 1:, :-1, :] + 0.5 * c0[..., :-1, 1:, :]
+        if ax == -3:
+            c0 = c
+        c = f
+    return c
+
+
+@pytest.mark.parametrize("dtype,tol", [("float64", 1e-14), ("float32", 1e-6)])
+@pytest.mark.parametrize("mt,nr", SHELLS)
+def test_prolongation_of_the_largest_values(tng, ctx, dtype, tol, mt, nr):
+    """Masks of the type's lowest and largest value: coarse nodes are copied to the bit and the
+    mean of such a value and an ordinary one is finite (a few roundings)."""
+    import torch
+    dt = getattr(torch, dtype)
+    mesh, om, lm, uid = shell(tng, ctx, mt, nr)
+    rng = np.random.default_rng(1)
+    c = rng.uniform(-1.0, 1.0, (3, uid[1].max() + 1, nr // 2 + 1))
+    big = float(torch.finfo(dt).max)
+    for comp, node, k, v in ((0, 0, 1, -big), (1, uid[1][1], 2, big), (2, uid[1].max(), 0, -big), (0, 7, nr // 2, big)):
+        c[comp, node, k] = v
+    ct = torch.tensor(c[:, uid[1]].reshape((3,) + mesh.shape(1)), device="cuda").to(dt).contiguous()
+    f = torch.full((3,) + mesh.shape(0), float("nan"), dtype=dt, device="cuda")
+    tng.prolong(ctx, mesh, 0, ct, f)
+    torch.cuda.synchronize()
+    assert torch.equal(f[:, :, ::2, ::2, ::2], ct)
+    want = to_fine(ct.double().cpu().numpy())
+    assert (np.abs(f.double().cpu().numpy() - want) <= tol * np.maximum(1.0, np.abs(want))).all()
