@@ -78,3 +78,30 @@ def test_prolongation_of_the_largest_values(tng, ctx, dtype, tol, mt, nr):
     assert torch.equal(f[:, :, ::2, ::2, ::2], ct)
     want = to_fine(ct.double().cpu().numpy())
     assert (np.abs(f.double().cpu().numpy() - want) <= tol * np.maximum(1.0, np.abs(want))).all()
+
+
+# a wedge at a five-ring vertex, one with an edge on a diamond's boundary, one inside
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("form", ["one point", "hourglass", "two points"])
+@pytest.mark.parametrize("cell", [(0, 0, 0, 1, 0), (3, 1, 0, 2, 1), (9, 1, 2, 3, 0)])
+@pytest.mark.parametrize("mt,nr", SHELLS)
+def test_diagonal_with_an_infinite_viscosity(tng, ctx, dtype, form, cell, mt, nr):
+    """Infinite at the wedge's nodes (positive terms), the same bits elsewhere."""
+    import torch
+    dt = getattr(torch, dtype)
+    mesh, om, lm, uid = shell(tng, ctx, mt, nr)
+    eta = torch.tensor(np.random.default_rng(2).uniform(0.5, 1.5, mesh.wedge_shape(0)), device="cuda").to(dt)
+    kw = {"hg_alpha": 0.1} if form == "hourglass" else {"twopoint": form == "two points"}
+    out = []
+    for v in (1.0, float("inf")):
+        eta[cell] = v
+        d = torch.full((3,) + mesh.shape(0), float("nan"), dtype=dt, device="cuda")
+        tng.diag_A(ctx, mesh, 0, eta, d, **kw)
+        torch.cuda.synchronize()
+        out.append(d.cpu().numpy())
+    q, i, j, k, w = cell
+    m1 = mt + 1
+    lat = [(q * m1 + i + a) * m1 + j + b for a, b in (((0, 0), (1, 0), (0, 1)), ((1, 1), (0, 1), (1, 0)))[w]]
+    hit = np.isin(uid[0], uid[0][lat]).reshape(10, m1, m1)[..., None] & np.isin(np.arange(nr + 1), (k, k + 1))
+    assert (out[1][:, hit] == np.inf).all()
+    assert np.array_equal(out[1][:, ~hit], out[0][:, ~hit])
