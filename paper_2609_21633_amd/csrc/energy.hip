@@ -239,12 +239,12 @@ __global__ void __launch_bounds__(256) buoyancy_kernel(EnergyGeo G, const double
     for (int x = threadIdx.x; x < nl * 6; x += 256) {
         const int cd = ring_tri[(size_t)lat0 * 6 + x];
         const int* rn = ring_nb + (size_t)lat0 * 6 + (x / 6) * 6;
-        nb[x] = rn[x % 6];
+        nb[x] = cd >= 0 ? rn[x % 6] : -1 - rn[x % 6];   // past the triangles of a five-ring: negative
         const int sl[3] = {lat0 + x / 6, rn[x % 6], rn[(x + 1) % 6]};
         double sc[3] = {0.0, 0.0, 0.0};
         for (int l = 0; l < 3; ++l)
             for (int c = 0; c < 3; ++c) sc[c] += unit[(size_t)sl[l] * 3 + c];
-        double w = 0.0;   // past the triangles of a five-ring
+        double w = 0.0;
         if (cd >= 0)
             w = G.geo[(size_t)(cd >> 3) * GEO_PER_COL + ((cd >> 2) & 1) * GEO_PER_TRI + 9] * (Ra / 36.0) /
                 sqrt(sc[0] * sc[0] + sc[1] * sc[1] + sc[2] * sc[2]);
@@ -263,7 +263,8 @@ __global__ void __launch_bounds__(256) buoyancy_kernel(EnergyGeo G, const double
         T v[7][2];
 #pragma unroll
         for (int r = 0; r < 7; ++r) {
-            const T* c = Tn + (size_t)(r < 6 ? nb[li * 6 + r] : lat0 + li) * n1;
+            const int q = r < 6 ? nb[li * 6 + r] : lat0 + li;
+            const T* c = Tn + (size_t)(r == 5 && q < 0 ? -1 - q : q) * n1;
             v[r][0] = c[k];
             v[r][1] = c[ka];
         }
@@ -275,13 +276,15 @@ __global__ void __launch_bounds__(256) buoyancy_kernel(EnergyGeo G, const double
             ta = 3.0 * (tbar[k] + tbar[ka]);
             wa *= 0.5 * (rhoalpha[k] + rhoalpha[ka]);
         }
+        const bool five = nb[li * 6 + 5] < 0;
         double acc[3] = {0.0, 0.0, 0.0};
         double sc[7];
 #pragma unroll
         for (int r = 0; r < 7; ++r) sc[r] = (double)v[r][0] + (double)v[r][1];
 #pragma unroll
         for (int r = 0; r < 6; ++r) {
-            const double s = sc[6] + (sc[r] + sc[r < 5 ? r + 1 : 0]) - ta;
+            double s = sc[6] + (sc[r] + sc[r < 5 ? r + 1 : 0]) - ta;
+            if (r == 5 && five) s = 0.0;   // not zero times a temperature that is not finite
 #pragma unroll
             for (int c = 0; c < 3; ++c) acc[c] += s * vec[li * 6 + r][c];
         }

@@ -105,3 +105,28 @@ def test_diagonal_with_an_infinite_viscosity(tng, ctx, dtype, form, cell, mt, nr
     hit = np.isin(uid[0], uid[0][lat]).reshape(10, m1, m1)[..., None] & np.isin(np.arange(nr + 1), (k, k + 1))
     assert (out[1][:, hit] == np.inf).all()
     assert np.array_equal(out[1][:, ~hit], out[0][:, ~hit])
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("at", ["vertex", "neighbour"])
+@pytest.mark.parametrize("mt,nr", SHELLS)
+def test_buoyancy_of_an_infinite_temperature(tng, ctx, dtype, at, mt, nr):
+    """Around the five-ring vertex on the z axis every direction has a positive z component: the
+    force there is infinite at the nodes of the wedges that hold the node, finite elsewhere."""
+    import torch
+    dt = getattr(torch, dtype)
+    mesh, om, lm, uid = shell(tng, ctx, mt, nr)
+    slot = 0 if at == "vertex" else 1          # (0, 0) of diamond 0 and the next node along j
+    node, k = lm.slot2lat[slot], 2
+    T = np.random.default_rng(3).uniform(0.0, 1.0, (om.n_lat, nr + 1))
+    T[node, k] = np.inf
+    f = torch.full((3,) + mesh.shape(0), float("nan"), dtype=dt, device="cuda")
+    tng.rhs_buoyancy(ctx, mesh, 0, torch.tensor(lm.to_lib(T.ravel()), device="cuda").to(dt), 1e5, f)
+    torch.cuda.synchronize()
+    near = np.unique(om.tris[(om.tris == node).any(axis=1)])
+    hit = np.zeros((om.n_lat, nr + 1), bool)
+    hit[near, k - 1:k + 2] = True
+    hit[:, [0, -1]] = False                    # no-slip rows are zero
+    fz = lm.from_lib(f[2].double().cpu().numpy()).reshape(om.n_lat, nr + 1)
+    assert (fz[hit] == np.inf).all()
+    assert np.isfinite(lm.from_lib(f.double().cpu().numpy())[~hit.ravel()]).all()
