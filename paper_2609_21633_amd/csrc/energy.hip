@@ -245,8 +245,12 @@ __global__ void __launch_bounds__(256) buoyancy_kernel(EnergyGeo G, const double
         for (int l = 0; l < 3; ++l)
             for (int c = 0; c < 3; ++c) sc[c] += unit[(size_t)sl[l] * 3 + c];
         double w = 0.0;
+        // the shape function's 1/6 and the mean's 1/6, not Ra / 36: its rounding is the same for
+        // every triangle and shifts the whole field (FP64 (8,16) 1.05e-15 -> 1.07e-15 of the
+        // field's norm off its value)
         if (cd >= 0)
-            w = G.geo[(size_t)(cd >> 3) * GEO_PER_COL + ((cd >> 2) & 1) * GEO_PER_TRI + 9] * (Ra / 36.0) /
+            w = G.geo[(size_t)(cd >> 3) * GEO_PER_COL + ((cd >> 2) & 1) * GEO_PER_TRI + 9] *
+                (Ra * (1.0 / 6.0) * (1.0 / 6.0)) /
                 sqrt(sc[0] * sc[0] + sc[1] * sc[1] + sc[2] * sc[2]);
         for (int c = 0; c < 3; ++c) vec[x][c] = cd >= 0 ? w * sc[c] : 0.0;
     }
