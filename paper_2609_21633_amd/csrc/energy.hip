@@ -207,7 +207,7 @@ __global__ void __launch_bounds__(256) energy_rhs_kernel(EnergyGeo G, const int*
             b[out0 + t] = T(k == 0 ? T_in : T_out);
             continue;
         }
-        const double ra = G.r_in + (k + 0.5) * G.dr, rb = ra - G.dr;
+        const double ra = G.r_in + (k + 0.5) * G.dr, rb = G.r_in + (k - 0.5) * G.dr;
         b[out0 + t] = T(ms[li] * (ra * ra + rb * rb) *
                         ((double)Tn[out0 + t] * inv_dt + (H ? (double)H[out0 + t] : 0.0)));
     }

@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(256) pmass_kernel(const T* __restrict__ eta, c
         const int I = I0 - 1 + li, J = J0 - 1 + lj, K = K0 - 1 + lk;
         double p[4][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
         if (I >= 0 && I < mc && J >= 0 && J < mc && K >= 0 && K < nc) {
-            const double r0 = r_in + (2 * K + 0.5) * dr, r1 = r0 + dr;
+            const double r0 = r_in + (2 * K + 0.5) * dr, r1 = r_in + (2 * K + 1.5) * dr;
             T e[2][2][4];
 #pragma unroll
             for (int a = 0; a < 2; ++a)
