@@ -316,13 +316,13 @@ void ring_launch(const tng_ctx* ctx, const Level& L, const RingArgs<T>& a, unsig
 
 }  // namespace
 
-// Where one gathered launch beats seam zeroing, streaming apply and update.  V-cycle times
-// with the levels' seven steps and residual streamed and gathered: (16,16) FP64 463 and 139
-// us, FP32 391 and 130 us (levels up to 49,130 slots); the level of 359,370 slots of a
-// (32,32) cycle FP64 450 and 388 us, FP32 about 350 and 253 us.  At 2.7 M slots ((64,64)) the
-// first gathered form took 43 us a step more than the streaming one in FP32 and 180 us in
-// FP64: the gathered form grows with the slots, the streaming one hardly below a million,
-// so the lines lie between the measured sizes.
+// Where one gathered launch beats seam zeroing, streaming apply and update.  A smoother step
+// gathered and streamed, FP64: (16,16), 49,130 slots, 6.7 and 19 us; (32,32), 359,370 slots, 28
+// and 35; (32,44), 490,050 slots, 36.2 and 37.1; (64,10), 464,750 slots, 36 and 69; (16,170),
+// 494,190 slots, 36 and 44.  FP32: (16,16) 4.7 and 20 us; (32,32) 14 and 30; (32,72), 794,970
+// slots, 29 and 43.  The gathered form grows with the slots (74 ps each in FP64, 37 in FP32),
+// the streaming one with the rows, so the forms meet near the FP64 line on the shells with the
+// fewest rows per slot; nothing is measured above either line.
 // A forced band count asks for the streaming form on every level.
 template <typename T>
 bool ring_apply_fits(const tng_ctx* ctx, const Level& L) {

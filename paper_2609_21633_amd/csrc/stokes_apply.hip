@@ -1324,13 +1324,18 @@ void band_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned fl
 }  // namespace
 
 // Small levels: the plain viscous block or full operator gathered per node in one launch
-// (ring_smooth.hip), unless a band count is forced.  The pressure rows gather 96 wedges per
-// coarse node, so the full operator takes this form on fewer nodes.  A call as a program
-// makes it (20 us of it in the caller's thread), gathered against streaming: viscous block
-// (8,8) FP32 20 against 23 us, (32,16) FP64 21 against 32, (32,64) FP32, 707,850 slots, 29
-// against 29; full operator (8,8) FP32 21 against 26 us, (16,16), 49,130 slots, FP64 23
-// against 28, but (16,64) FP32, 187,850 slots, 36 against 26 and (16,60) FP64 74 against 28.
-constexpr long long RING_K_SLOTS = 60000;
+// (ring_smooth.hip), unless a band count is forced.  A call as a program makes it (20 us of
+// it in the caller's thread), gathered against streaming:
+//   viscous block FP32 19 against 22 to 42 us up to 500,000 slots, (32,72), 794,970 slots,
+//     28 against 37; FP64 19 against 25 to 31 up to 250,000, (32,40), 446,490 slots, 32.6
+//     against 32.7, (32,44), 490,050 slots, 35.2 against 32.4, but (64,10), 464,750 slots, 37
+//     against 66 and (16,170), 494,190 slots, 36 against 38: gathering takes 73 ps a slot,
+//     streaming on one-stretch columns about 1 us a cell row whatever their length (longer
+//     columns more), so those meet at RING_A_ROW_SLOTS slots a row;
+//   full operator (the pressure rows gather 96 wedges per coarse node) (16,16), 49,130 slots,
+//     20 against 26 to 27 us, (8,72), 59,130 slots, FP64 23 against 27, but (16,64) FP32,
+//     187,850 slots, 36 against 26 and (16,60) FP64 74 against 28.
+constexpr long long RING_K_SLOTS = 60000, RING_A_ROW_SLOTS = 14000;
 template <typename T>
 bool small_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned flags, double hg_alpha, const void* eta,
                  const void* const u[3], const void* p, void* const yu[3], void* yp) {
@@ -1338,6 +1343,8 @@ bool small_apply(const tng_ctx* ctx, const Level& L, const Level* Lp, unsigned f
     if ((hg_alpha != 0.0 && (ops & TNG_OP_A)) ||
         (ops != TNG_OP_A && ops != (TNG_OP_A | TNG_OP_BT | TNG_OP_B)) || !ring_apply_fits<T>(ctx, L) ||
         (ops != TNG_OP_A && L.node_slots() > RING_K_SLOTS))
+        return false;
+    if (std::is_same<T, double>::value && ops == TNG_OP_A && L.n <= 64 && L.node_slots() > RING_A_ROW_SLOTS * L.m)
         return false;
     ring_apply<T>(ctx, L, Lp, flags, eta, u, p, yu, yp);
     return true;

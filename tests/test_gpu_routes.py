@@ -151,3 +151,21 @@ def test_gathered_solver_applies_are_timed(tng, profiled):
     s.vcycle(b, torch.empty_like(b))
     assert applies(profiled) == {"A/8x8/ring": 6, "A/4x4/ring": 6}
     s.close()
+
+
+# the viscous block alone in FP64: columns of one stretch stream above 14,000 slots a cell row
+@pytest.mark.parametrize("mt,nr,form", [(32, 38, "ring"), (32, 44, "stream"), (64, 8, "ring"), (16, 64, "ring"),
+                                        (16, 160, "ring")])
+def test_form_of_the_viscous_block(tng, profiled, mt, nr, form):
+    import torch
+    mesh = tng.Mesh(profiled, mt, nr, levels=1)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    eta = 0.5 + torch.rand(mesh.wedge_shape(0), generator=g, dtype=torch.float64, device="cuda")
+    u = torch.ones((3,) + mesh.shape(0), dtype=torch.float64, device="cuda") * torch.rand(
+        nr + 1, generator=g, dtype=torch.float64, device="cuda")      # the same in all copies
+    y = [torch.full_like(u, float("nan")) for _ in range(2)]
+    tng.stokes_apply(profiled, mesh, 0, tng.OP_A | tng.OP_DIRICHLET, eta, u, None, y[0], None)
+    assert [k.rstrip("0123456789") for k in applies(profiled)] == [f"A/{mt}x{nr}/" + ("ring" if form == "ring" else "b")]
+    profiled.set_apply_bands(3)
+    tng.stokes_apply(profiled, mesh, 0, tng.OP_A | tng.OP_DIRICHLET, eta, u, None, y[1], None)
+    assert float((y[0] - y[1]).abs().max()) <= 1e-13 * float(y[1].abs().max())
