@@ -399,15 +399,6 @@ __global__ void __launch_bounds__(256) zero_tile_seams_kernel(T* y, int m, unsig
 
 // Dirichlet temperature rows of the result: y = T on k = 0 and k = n
 template <typename T>
-__global__ void copy_layers_kernel(long long ncol, int n, T* y, const T* src) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 2 * ncol) return;
-    const long long idx = (t >> 1) * (n + 1) + ((t & 1) ? n : 0);
-    y[idx] = src[idx];
-}
-
-// Dirichlet temperature rows of the result: y = T on k = 0 and k = n
-template <typename T>
 __global__ void copy_layers_kernel(unsigned ncol, int n, T* y, const T* src) {
     const unsigned t = blockIdx.x * 256u + threadIdx.x;
     if (t >= 2 * ncol) return;
@@ -484,13 +475,13 @@ void energy_apply_stream(const tng_ctx* ctx, const Level& L, const T* const u[3]
             launch_stream<T, false, 4, 4>(ctx, L, a);
     }
     void* f[1] = {y};
-    if (std::is_same<T, double>::value) {
+    if constexpr (std::is_same<T, double>::value) {
         launch_interface(ctx, L, prec_of<T>(), 2, 1, f);   // the spheres' rows are complete
-        return;
+    } else {
+        launch_interface(ctx, L, prec_of<T>(), 0, 1, f);
+        copy_layers_kernel<T><<<nblk(2 * L.lat_slots(), 256), 256, 0, ctx->stream>>>((unsigned)L.lat_slots(), L.n, y, Tin);
+        TNG_HIP(hipGetLastError());
     }
-    launch_interface(ctx, L, prec_of<T>(), 0, 1, f);
-    copy_layers_kernel<T><<<nblk(2 * L.lat_slots(), 256), 256, 0, ctx->stream>>>((unsigned)L.lat_slots(), L.n, y, Tin);
-    TNG_HIP(hipGetLastError());
 }
 
 template void energy_apply_stream<double>(const tng_ctx*, const Level&, const double* const[3], double, const double*,

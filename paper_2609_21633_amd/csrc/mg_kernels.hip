@@ -24,20 +24,6 @@ inline void check_counts(const SlotBatch& sb) {
         TNG_REQUIRE(sb.cnt[z] >= 1 && sb.cnt[z] <= MAX_MDOT, "per-slot vector count out of range");
 }
 
-struct NodeIdx {
-    int d, i, j, k;
-};
-__device__ __forceinline__ NodeIdx decode_node(long long t, int m, int n) {
-    NodeIdx r;
-    r.k = (int)(t % (n + 1));
-    t /= (n + 1);
-    r.j = (int)(t % (m + 1));
-    t /= (m + 1);
-    r.i = (int)(t % (m + 1));
-    r.d = (int)(t / (m + 1));
-    return r;
-}
-
 // Gradient of the wedge basis function of local node (lat, top) at q_c, with
 // the constants folded as in wedge.hpp: sign pattern of the reference gradient
 // times the folded rows of G^{-1}.

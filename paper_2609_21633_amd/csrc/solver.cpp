@@ -506,7 +506,7 @@ void remove_pressure_mean(tng_solver* s) {
 // ---- setup ----------------------------------------------------------------
 void build_coarse_maps(tng_solver* s) {
     const Level& C = s->mesh->lv[s->nlev - 1];
-    const int m = C.m, n = C.n;
+    const int n = C.n;
     const long long nl = C.lat_slots(), nsl = C.node_slots();
     // owner slot of every unique lateral id
     std::vector<int> owner_of(C.n_unique_lat, -1);

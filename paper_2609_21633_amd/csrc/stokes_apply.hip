@@ -76,11 +76,6 @@ struct BandArgs {
     const T* __restrict__ rho;    // [n+1] reference density at the node layers (TALA)
 };
 
-template <typename T>
-__device__ __forceinline__ T shfl_up1(T v, int lane) {
-    return __shfl(v, (lane + 63) & 63, 64);
-}
-
 // Element idx of a field addressed by a 32-bit byte offset from its (wave-uniform)
 // base, so that the compiler can use the scalar-base addressing form (64-bit base in
 // scalar registers, 32-bit offset per lane) instead of a 64-bit address per lane; the
