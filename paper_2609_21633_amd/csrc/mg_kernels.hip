@@ -1417,9 +1417,9 @@ __global__ void rand_kernel(unsigned n, unsigned long long seed, T* a) {
     }
 }
 
-// y <- x / sqrt(s[0])  (normalise by a device-side squared norm)
+// y <- x / sqrt(s[0])  (normalise by a device-side squared norm; y may be x)
 template <typename T>
-__global__ void scale_rsqrt_kernel(unsigned n, const double* __restrict__ s, const T* __restrict__ x, T* y,
+__global__ void scale_rsqrt_kernel(unsigned n, const double* __restrict__ s, const T* x, T* y,
                                    SlotBatch sb) {
     const long long so = slot_off(sb);
     s = at_slot(s, so);
