@@ -372,8 +372,8 @@ void precond(tng_solver* s, const T* v, T* z) {
 // One V-cycle on the caller's velocity fields: straight on them when their components
 // follow one another as in the solver's vectors, 16-byte aligned and without overlap
 // ((128,128) FP32: 0.2 ms of copies less), else through copies.  Launched from the host:
-// replayed as a graph the cycle is slower at every size ((8,8) FP64 94 -> 145 us, (32,32)
-// 464 -> 541 us: about 1.5 us more between two kernels).
+// replayed as a graph the cycle was slower at every size ((8,8) FP64 94 -> 145 us, (32,32),
+// then of more kernels, 464 -> 541 us: about 1.5 us more between two kernels).
 template <typename T>
 void vcycle_fields(tng_solver* s, const T* const b[3], T* const x[3]) {
     const long long ns = s->ns0, n3 = 3 * ns;
