@@ -1,5 +1,7 @@
 """Which kernels a call takes, and parity of the ones that the default choice leaves to larger
 shells than the oracle's: small levels gather per node unless a band count is forced."""
+import time
+
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -350,7 +352,7 @@ def test_batched_streaming_matches_single(tng, ctx, mt, mixed, tol):
     single = None if mixed else tng.StokesSolver(ctx, mesh, **opts)
 
     def rel(a, b):
-        return max(float((x - y).norm() / y.norm()) for x, y in zip(a, b))
+        return float(np.max([float((x - y).norm() / y.norm()) for x, y in zip(a, b)]))   # NaN stays NaN
 
     def out():
         return (torch.empty((3,) + mesh.shape(0), dtype=torch.float64, device="cuda"),
@@ -372,14 +374,27 @@ def test_batched_streaming_matches_single(tng, ctx, mt, mixed, tol):
             assert rel(alone, own) <= tol
         reqs.append((Tt, 1.0 + i, alone, out()))
     torch.cuda.synchronize()
-    tickets = [srv.submit(0, Tt, lc, 1e5, *got) for Tt, lc, _, got in reqs]
-    srv.wait(0)
-    assert srv.stats()["slots"] == 3
-    for t, (_, lc, alone, got) in zip(tickets, reqs):
-        assert srv.poll(t)["inner_its"] == 10
-        d = rel(got, alone)
-        print(f"({mt},{mt}) mixed={mixed} contrast 1e{lc:.0f}: in the batch against alone {d:.1e}", flush=True)
-        assert d <= tol
+    # a pause of this thread between two submissions (a garbage collection) can outlast a solve, the
+    # third then takes an idle slot: the group is sent again until all three ran at one time
+    for attempt in range(20):
+        for _, _, _, got in reqs:
+            for x in got:
+                x.fill_(float("nan"))
+        torch.cuda.synchronize()
+        sent = [(time.perf_counter(), srv.submit(0, Tt, lc, 1e5, *got)) for Tt, lc, _, got in reqs]
+        srv.wait(0)
+        infos = [srv.poll(t) for _, t in sent]
+        for info, (_, lc, alone, got) in zip(infos, reqs):
+            assert info["inner_its"] == 10
+            d = rel(got, alone)
+            print(f"({mt},{mt}) mixed={mixed} contrast 1e{lc:.0f}: in the batch against alone {d:.1e}", flush=True)
+            assert d <= tol
+        starts = [t0 + info["queue"] for (t0, _), info in zip(sent, infos)]
+        ends = [t0 + info["latency"] for (t0, _), info in zip(sent, infos)]
+        if srv.stats()["slots"] == 3 and max(starts) < min(ends):
+            break
+    else:
+        raise AssertionError(f"never three at one time: {srv.stats()}, {infos}")
     if single:
         single.close()
     srv.close()
